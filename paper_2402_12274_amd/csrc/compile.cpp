@@ -443,6 +443,9 @@ Layout finalize(const LayoutP &L0)
         again = false;
         for (size_t s = 0; s < L.shapes.size(); s++) {
             if (L.shapes[s].loops.size() <= (size_t)MAXI) continue;
+            // a shape already expanded stays listed until the unused are dropped below
+            if (std::none_of(L.groups.begin(), L.groups.end(), [s](const Group &g) { return g.shape == (int32_t)s; }))
+                continue;
             Shape S = L.shapes[s];
             Shape T = S;
             T.loops.erase(T.loops.begin());
