@@ -6,7 +6,7 @@ import pytest
 from oracle import build_type as obuild
 from paper_2402_12274_amd import inputs, mdt
 
-DARRAY = ("darray", 8, 3, [47, 60, 60], ["cyclic"] * 3, [5] * 3, [2, 2, 2], "C", inputs.DOUBLE)
+DARRAY = ("darray", 8, 3, [93, 104, 104], ["cyclic"] * 3, [5] * 3, [2, 2, 2], "C", inputs.DOUBLE)
 
 
 @pytest.mark.timeout(60, method="thread")
