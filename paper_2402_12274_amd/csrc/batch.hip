@@ -772,7 +772,8 @@ std::string shape_key(mdt_batch_s *b, int ncu)
     h = fnv1a(h, (uint64_t)mdt_version());
     h = fnv1a(h, (uint64_t)ncu);
     for (const BatchReq &r : b->reqs) {
-        h = fnv1a(h, ((uint64_t)r.d.unpack << 48) | ((uint64_t)r.d.body << 32) | (uint64_t)(uint32_t)r.d.kind);
+        h = fnv1a(h, ((uint64_t)r.d.unpack << 48) | ((uint64_t)r.d.body << 32) |
+                         (uint64_t)(uint32_t)r.type->comp->host.kind);
         h = fnv1a(h, (uint64_t)r.type->size);
         h = fnv1a(h, (uint64_t)(r.type->comp ? r.type->comp->nruns : 0));
         h = fnv1a(h, (uint64_t)(64 - __builtin_clzll((uint64_t)r.d.nbytes | 1)));
@@ -985,7 +986,8 @@ MDT_API int mdt_batch_add_pack(mdt_batch b, const void *inbuf, mdt_count incount
         A.elem1 = A.off + A.nbytes <= D->lay.size;
         int32_t lds = 0;
         const int body = body_of(D->lay, A, false, &lds);
-        ReqDesc d{(uint64_t)(uintptr_t)D->d_lay, A.typed, A.packed, A.off, A.nbytes, A.head, A.nchunks, 0, D->lay.kind, A.elem1, body};
+        ReqDesc d{(uint64_t)(uintptr_t)D->d_lay, A.typed, A.packed, A.off, A.nbytes, A.head, A.nchunks, 0,
+                  xfer_kind(D->lay, A.elem1), A.elem1, body};
         rc = add_req(b, reinterpret_cast<TypeNode *>(t), d, lds);
         if (rc) return rc;
     }
@@ -1011,7 +1013,8 @@ MDT_API int mdt_batch_add_unpack(mdt_batch b, const void *inbuf, mdt_count insiz
         A.elem1 = A.off + A.nbytes <= D->lay.size;
         int32_t lds = 0;
         const int body = body_of(D->lay, A, true, &lds);
-        ReqDesc d{(uint64_t)(uintptr_t)D->d_lay, A.typed, A.packed, A.off, A.nbytes, A.head, A.nchunks, 1, D->lay.kind, A.elem1, body};
+        ReqDesc d{(uint64_t)(uintptr_t)D->d_lay, A.typed, A.packed, A.off, A.nbytes, A.head, A.nchunks, 1,
+                  xfer_kind(D->lay, A.elem1), A.elem1, body};
         rc = add_req(b, reinterpret_cast<TypeNode *>(t), d, lds);
         if (rc) return rc;
     }
@@ -1097,11 +1100,11 @@ MDT_API int mdt_batch_add_relay(mdt_batch b, const void *src, mdt_count srccount
         d.head = A.head;
         d.nchunks = A.nchunks;
         d.unpack = 0;
-        d.kind = Ds->lay.kind;
+        d.kind = xfer_kind(Ds->lay, A.elem1);
         d.elem1 = A.elem1;
         d.body = BODY_RELAY;
         d.lay2 = (uint64_t)(uintptr_t)Dd->d_lay;
-        d.kind2 = Dd->lay.kind;
+        d.kind2 = xfer_kind(Dd->lay, U.elem1);
         d.elem1_2 = U.elem1;
         d.typed2 = U.typed;
         d.pbody = body_of(Ds->lay, A, false, &lds_p);

@@ -120,11 +120,13 @@ __device__ __forceinline__ void run_tile(const DevLayout &L, const XferArgs &A, 
             int64_t s1 = s0 + 1024 < cend ? s0 + 1024 : cend;
             if (UNPACK) {
                 if (kind == KIND_CONTIG) unpack_tile4<KIND_CONTIG>(L, A, s0, s1);
+                else if (kind == KIND_STRIDED) unpack_tile4<KIND_STRIDED>(L, A, s0, s1);
                 else if (kind == KIND_SINGLE) unpack_tile4<KIND_SINGLE>(L, A, s0, s1);
                 else unpack_tile4<KIND_MULTI>(L, A, s0, s1);
             } else {
                 constexpr bool CACHED = (BODY & BODY_CACHED) != 0;
                 if (kind == KIND_CONTIG) pack_tile4<KIND_CONTIG, CACHED>(L, A, s0, s1);
+                else if (kind == KIND_STRIDED) pack_tile4<KIND_STRIDED, CACHED>(L, A, s0, s1);
                 else if (kind == KIND_SINGLE) pack_tile4<KIND_SINGLE, CACHED>(L, A, s0, s1);
                 else pack_tile4<KIND_MULTI, CACHED>(L, A, s0, s1);
             }

@@ -873,6 +873,50 @@ void lower_records(const Layout &L, Compiled &C)
     R.count1_only = count1;
 }
 
+// The compact program of a layout of one group: the outer loops and the
+// shape's loops as levels, and leaf runs of one length and spacing (a short
+// loop that normalisation unrolled) as one more.  Spans of one byte have no
+// 32-bit magic number and stay with the general program.
+void lower_strided(const Layout &L, Compiled &C)
+{
+    DevLayout &D = C.host;
+    DevStrided &T = D.st;
+    std::memset(&T, 0, sizeof T);
+    if (L.groups.size() != 1 || D.kind == KIND_CONTIG || D.kind == KIND_EMPTY) return;
+    const Shape &S = L.shapes[0];
+    if (S.varlen || S.implicit0 || S.leaf.empty() || L.size < 2 || L.size >= ((int64_t)1 << 30)) return;
+    const int64_t run = S.leaf[0].len;
+    int64_t step = S.leaf.size() > 1 ? S.leaf[1].off - S.leaf[0].off : 0;
+    for (size_t j = 0; j < S.leaf.size(); j++)
+        if (S.leaf[j].len != run || S.leaf[j].off != S.leaf[0].off + (int64_t)j * step) return;
+    std::vector<Loop> lv = L.outer;
+    lv.insert(lv.end(), S.loops.begin(), S.loops.end());
+    if (S.leaf.size() > 1) lv.push_back(Loop{(int64_t)S.leaf.size(), step});
+    if (lv.size() > (size_t)STRIDED_MAX) return;
+    auto fits = [](int64_t v) { return v >= INT32_MIN && v <= INT32_MAX; };
+    int64_t span = run;
+    for (size_t l = lv.size(); l-- > 0;) {
+        if (span < 2 || !fits(lv[l].stride)) return;
+        const MagicDiv32 d = make_magic32((uint32_t)span);
+        T.m[l] = d.m;
+        T.s[l] = d.s;
+        T.span[l] = (uint32_t)span;
+        T.stride[l] = (int32_t)lv[l].stride;
+        span *= lv[l].cnt;
+    }
+    T.nl = (int32_t)lv.size();
+    T.elem1_only = !fits(D.extent);
+    T.run = (uint32_t)run;
+    T.size = (uint32_t)L.size;
+    const MagicDiv32 c = make_magic32(T.size);
+    T.cm = c.m;
+    T.cs = c.s;
+    T.extent = D.extent;
+    T.base = L.groups[0].disp + S.leaf[0].off;
+    T.dsize = D.dsize;
+    T.on = 1;
+}
+
 std::shared_ptr<Compiled> make_compiled(TypeNode *t)
 {
     LayoutP L0 = compile_node(t);
@@ -880,6 +924,7 @@ std::shared_ptr<Compiled> make_compiled(TypeNode *t)
     C->layout = std::make_shared<Layout>(finalize(L0));
     lower(t, *C->layout, *C);
     lower_records(*C->layout, *C);
+    lower_strided(*C->layout, *C);
     return C;
 }
 

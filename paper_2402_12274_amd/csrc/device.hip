@@ -188,6 +188,23 @@ __global__ __launch_bounds__(256) void xfer_kernel(const DevLayout L, const Xfer
     }
 }
 
+// regular layouts: the same tiles through the compact program, which is a
+// fifth of the general descriptor to pass (a 1.2 KB argument costs 0.75 us a
+// launch: 4.3 against 3.6 us back to back)
+template <int NL, bool UNPACK>
+__global__ __launch_bounds__(256) void strided_kernel(const DevStrided S, const XferArgs A)
+{
+    const int64_t ntiles = (A.nchunks + A.tile_chunks - 1) / A.tile_chunks;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int64_t c0 = t * A.tile_chunks;
+        const int64_t cend = c0 + A.tile_chunks < A.nchunks ? c0 + A.tile_chunks : A.nchunks;
+        const Tile T(A, c0, cend);
+        const StridedAt<NL> at(S, T.p0, A.elem1);
+        if (UNPACK) unpack_tile_at(at, A, T);
+        else pack_tile_at<false>(at, A, T);
+    }
+}
+
 // typed copy: one tile of 1024 chunks per workgroup (four per lane)
 template <int KS, int KD>
 __global__ __launch_bounds__(256) void copy_kernel(const DevLayout Ls, const DevLayout Ld, const CopyArgs A)
@@ -360,6 +377,17 @@ bool use_dense(const DevLayout &L, const XferArgs &A, bool unpack)
 
 bool use_runs(const DevLayout &L) { return L.kind == KIND_MULTI && L.runs_only && runs_enabled(); }
 
+// the kernel compiled for the layout's number of levels
+template <int NL>
+static void launch_strided(const DevStrided &S, const XferArgs &A, bool unpack, dim3 g, hipStream_t s)
+{
+    if constexpr (NL > 0) {
+        if (S.nl < NL) return launch_strided<NL - 1>(S, A, unpack, g, s);
+    }
+    if (unpack) hipLaunchKernelGGL((strided_kernel<NL, true>), g, dim3(256), 0, s, S, A);
+    else hipLaunchKernelGGL((strided_kernel<NL, false>), g, dim3(256), 0, s, S, A);
+}
+
 int launch_xfer(const DevLayout &L, const XferArgs &A0, bool unpack, hipStream_t s)
 {
     if (A0.nbytes == 0 || L.kind == KIND_EMPTY) return MDT_SUCCESS;
@@ -386,6 +414,11 @@ int launch_xfer(const DevLayout &L, const XferArgs &A0, bool unpack, hipStream_t
     if (A.tile_chunks <= 0 || A.tile_chunks > 1024) A.tile_chunks = default_tile_chunks(A.nchunks);
     int64_t grid = launch_grid((A.nchunks + A.tile_chunks - 1) / A.tile_chunks);
     dim3 g((unsigned)grid), b(256);
+    if (xfer_kind(L, A.elem1) == KIND_STRIDED) {
+        launch_strided<STRIDED_MAX>(L.st, A, unpack, g, s);
+        HIPCHK(hipGetLastError());
+        return MDT_SUCCESS;
+    }
 #define LAUNCH(K)                                                                    \
     do {                                                                             \
         if (unpack) hipLaunchKernelGGL((xfer_kernel<K, true>), g, b, 0, s, L, A);    \

@@ -198,319 +198,324 @@ __device__ __forceinline__ void scatter(const V4 &acc, int k, uint8_t *d, int n)
 }
 
 // ---------------------------------------------------------------------------
+// locators: where byte `rel` of a tile (counted from the tile's first packed
+// byte) lies in the typed buffer, and how many bytes of its run follow.  A
+// tile's first byte is located once per workgroup with scalar 64-bit
+// arithmetic; the lanes' positions inside the tile are 32-bit.
+
+// the general layout program
+template <int KIND>
+struct GenericAt {
+    const DevLayout &L;
+    uint64_t p0;
+    bool elem1;
+    __device__ __forceinline__ GenericAt(const DevLayout &L_, uint64_t p, int32_t e1) : L(L_), p0(p), elem1(e1 != 0) {}
+    __device__ __forceinline__ Loc32 operator()(uint32_t rel) const
+    {
+        const Loc l = locate<KIND>(L, p0 + rel, elem1);
+        return Loc32{l.addr, (int32_t)(l.rem < (int64_t)INT32_MAX ? l.rem : (int64_t)INT32_MAX)};
+    }
+    // the run at rel = 0 may hold n bytes
+    __device__ __forceinline__ bool run_may_hold(uint32_t) const { return true; }
+};
+
+// the compact program of a regular layout
+template <int NL = -1>
+struct StridedAt {
+    const DevStrided &S;
+    int64_t addr0;
+    uint32_t q0;
+    bool elem1;
+    __device__ __forceinline__ StridedAt(const DevStrided &S_, uint64_t p, int32_t e1) : S(S_), elem1(e1 != 0)
+    {
+        addr0 = S.base;
+        if (elem1) {
+            q0 = (uint32_t)p;
+        } else {
+            const uint64_t e = magic_div(p, S.dsize);
+            q0 = (uint32_t)(p - e * S.size);
+            addr0 += (int64_t)e * S.extent;
+        }
+    }
+    __device__ __forceinline__ Loc32 operator()(uint32_t rel) const { return locate_strided<NL>(S, q0 + rel, addr0, elem1); }
+    __device__ __forceinline__ bool run_may_hold(uint32_t n) const { return S.run >= n; }
+};
+
+// A tile: chunks [c0, cend) of a transfer (at most 2^17 of them), in 32-bit
+// positions from its first packed byte.
+struct Tile {
+    uint8_t *chunk0;  // packed address of chunk c0 (16-byte aligned)
+    uint64_t p0;      // stream position of the tile's first packed byte
+    int32_t r0;       // chunk c0's first byte, from the tile's first (-15 .. 0)
+    int32_t n;        // packed bytes of the tile
+    int32_t nc;       // chunks of the tile
+    __device__ __forceinline__ Tile(const XferArgs &A, int64_t c0, int64_t cend)
+    {
+        const int64_t lo = 16 * c0 - A.head;
+        const int64_t first = lo > 0 ? lo : 0, end = min(16 * cend - A.head, A.nbytes);
+        chunk0 = A.packed + lo;
+        p0 = (uint64_t)(A.off + first);
+        r0 = (int32_t)(lo - first);
+        n = (int32_t)(end - first);
+        nc = (int32_t)(cend - c0);
+    }
+    // chunk k (from c0) lies whole inside the transfer's range; rel: its first byte
+    __device__ __forceinline__ bool whole(int32_t k, int32_t &rel) const
+    {
+        rel = r0 + 16 * k;
+        return k < nc && rel >= 0 && rel + 16 <= n;
+    }
+};
+
+// ---------------------------------------------------------------------------
 // chunk bodies
 
-template <int KIND, bool CACHED>
-__device__ __forceinline__ void pack_chunk(const DevLayout &L, const XferArgs &A, int64_t c)
+// A chunk's n bytes from `rel` on, as chunk bytes [k, k + n), run by run.
+// The first two runs are located before either is read, so their loads are
+// in flight together (chunks of small blocks mostly hold two runs).
+template <class AT>
+__device__ __forceinline__ V4 gather_runs(const AT &at, const uint8_t *typed, uint32_t rel, int k, int n)
 {
-    int64_t lo = 16 * c - A.head;
-    int64_t a = lo > 0 ? lo : 0;
-    int64_t b = lo + 16 < A.nbytes ? lo + 16 : A.nbytes;
-    int k = (int)(a - lo);
-    int n = (int)(b - a);
-    uint64_t p = (uint64_t)(A.off + a);
     V4 acc = {0u, 0u, 0u, 0u};
-    const uint8_t *src = A.typed;
-    Loc l = locate<KIND>(L, p, A.elem1);
-    if (n == 16 && l.rem >= 16) {
-        acc = load16<CACHED>(src + l.addr);
-    } else {
-        // the first two runs are located before either is read, so their
-        // loads are in flight together (chunks of small blocks mostly hold
-        // two runs); further runs follow one at a time
-        int take = l.rem < n ? (int)l.rem : n;
-        int take2 = 0;
-        Loc l2 = l;
-        if (take > 0 && take < n) {
-            l2 = locate<KIND>(L, p + (uint64_t)take, A.elem1);
-            take2 = l2.rem < n - take ? (int)l2.rem : n - take;
-            if (take2 < 0) take2 = 0;
-        }
-        if (take > 0) gather_piece(acc, k, src + l.addr, take);
-        if (take2 > 0) gather_piece(acc, k + take, src + l2.addr, take2);
-        if (take > 0 && take2 > 0 && take + take2 < n) {
-            p += (uint64_t)(take + take2);
-            k += take + take2;
-            n -= take + take2;
-            l = locate<KIND>(L, p, A.elem1);
-            for (;;) {
-                int t = l.rem < n ? (int)l.rem : n;
-                if (t <= 0) break;  // unreachable for a well-formed layout; never spin
-                gather_piece(acc, k, src + l.addr, t);
-                p += t;
-                k += t;
-                n -= t;
-                if (n <= 0) break;
-                l = locate<KIND>(L, p, A.elem1);
-            }
-        }
+    Loc32 l = at(rel);
+    const int t1 = l.rem < n ? l.rem : n;
+    int t2 = 0;
+    Loc32 l2 = l;
+    if (t1 > 0 && t1 < n) {
+        l2 = at(rel + (uint32_t)t1);
+        t2 = l2.rem < n - t1 ? l2.rem : n - t1;
+        if (t2 < 0) t2 = 0;
     }
-    uint8_t *dst = A.packed - A.head + 16 * c;
-    if (a == lo && b == lo + 16) {
-        u32x4 v = {acc.w0, acc.w1, acc.w2, acc.w3};
-        store_out(A, dst, v);
-    } else {
-        for (int i = (int)(a - lo); i < (int)(b - lo); i++) gptr(dst)[i] = (uint8_t)byte_at(acc, i);
+    if (t1 > 0) gather_piece(acc, k, typed + l.addr, t1);
+    if (t2 > 0) gather_piece(acc, k + t1, typed + l2.addr, t2);
+    int done = t1 + t2;
+    while (t2 > 0 && done < n) {
+        l = at(rel + (uint32_t)done);
+        const int t = l.rem < n - done ? l.rem : n - done;
+        if (t <= 0) break;  // unreachable for a well-formed layout; never spin
+        gather_piece(acc, k + done, typed + l.addr, t);
+        done += t;
     }
+    return acc;
 }
 
-template <int KIND>
-__device__ __forceinline__ void unpack_chunk(const DevLayout &L, const XferArgs &A, int64_t c)
+// Load a whole chunk when its bytes lie in one run or in two dword-aligned
+// runs; false when it needs the general body.
+template <bool CACHED, class AT>
+__device__ __forceinline__ bool gather_fast(const AT &at, const uint8_t *typed, uint32_t rel, V4 &acc)
 {
-    int64_t lo = 16 * c - A.head;
-    int64_t a = lo > 0 ? lo : 0;
-    int64_t b = lo + 16 < A.nbytes ? lo + 16 : A.nbytes;
-    int k = (int)(a - lo);
-    int n = (int)(b - a);
-    // the aligned 16-byte block holding this chunk's packed bytes
-    const uint8_t *in = A.packed - A.head + 16 * c;
-    u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)in));
-    V4 acc = {v.x, v.y, v.z, v.w};
-    uint64_t p = (uint64_t)(A.off + a);
-    uint8_t *dst = const_cast<uint8_t *>(A.typed);
-    Loc l = locate<KIND>(L, p, A.elem1);
+    const Loc32 l = at(rel);
+    if (l.rem >= 16) {
+        acc = load16<CACHED>(typed + l.addr);
+        return true;
+    }
+    // two runs split on a dword boundary, both dword aligned (blocks of
+    // float64 or int32 at a stride): independent loads, each from whichever
+    // run holds that word
+    const uintptr_t a1 = (uintptr_t)(typed + l.addr);
+    const int t1 = l.rem;
+    if (((a1 | (uintptr_t)t1) & 3) != 0) return false;
+    const Loc32 l2 = at(rel + (uint32_t)t1);
+    const uintptr_t a2 = (uintptr_t)(typed + l2.addr) - (uintptr_t)t1;  // chunk byte j of run 2 at a2 + j
+    if (l2.rem < 16 - t1 || (a2 & 3) != 0) return false;
+    if (t1 == 8 && ((a1 | a2) & 7) == 0) {
+        // two 8-byte blocks (float64 at a stride): one request each
+        const u32x2 x = *gptr((const u32x2 *)a1);
+        const u32x2 y = *gptr((const u32x2 *)(a2 + 8));
+        acc = V4{x.x, x.y, y.x, y.y};
+        return true;
+    }
+    acc.w0 = *gptr((const uint32_t *)(0 < t1 ? a1 : a2));
+    acc.w1 = *gptr((const uint32_t *)(4 < t1 ? a1 + 4 : a2 + 4));
+    acc.w2 = *gptr((const uint32_t *)(8 < t1 ? a1 + 8 : a2 + 8));
+    acc.w3 = *gptr((const uint32_t *)(12 < t1 ? a1 + 12 : a2 + 12));
+    return true;
+}
+
+// Chunk bytes [k, k + n) to the typed bytes from `rel` on, run by run (l:
+// the first run).  Stores do not wait, so a lane's chunks overlap.
+template <class AT>
+__device__ __forceinline__ void scatter_runs(const AT &at, uint8_t *typed, uint32_t rel, Loc32 l, int k, int n,
+                                             const V4 &acc)
+{
+    int done = 0;
     for (;;) {
-        int take = l.rem < n ? (int)l.rem : n;
-        if (take <= 0) break;  // unreachable for a well-formed layout; never spin
-        scatter(acc, k, dst + l.addr, take);
-        p += take;
-        k += take;
-        n -= take;
-        if (n <= 0) break;
-        l = locate<KIND>(L, p, A.elem1);
+        const int t = l.rem < n - done ? l.rem : n - done;
+        if (t <= 0) break;  // unreachable for a well-formed layout; never spin
+        scatter(acc, k + done, typed + l.addr, t);
+        done += t;
+        if (done >= n) break;
+        l = at(rel + (uint32_t)done);
     }
 }
 
-// Load chunk c whole when its bytes lie in one run or in two dword-aligned
-// runs; false when it needs the general body (or lies outside the tile).
-template <int KIND, bool CACHED>
-__device__ __forceinline__ bool pack_first(const DevLayout &L, const XferArgs &A, int64_t c, int64_t cend, V4 &acc)
+// Store a whole chunk to the typed side.
+template <class AT>
+__device__ __forceinline__ void scatter_chunk(const AT &at, uint8_t *typed, uint32_t rel, const Loc32 &l, const V4 &acc)
 {
-    int64_t lo = 16 * c - A.head;
-    if (c < cend && lo >= 0 && lo + 16 <= A.nbytes) {
-        Loc l = locate<KIND>(L, (uint64_t)(A.off + lo), A.elem1);
-        if (l.rem >= 16) {
-            acc = load16<CACHED>(A.typed + l.addr);
-            return true;
+    if (l.rem >= 16) {
+        scatter(acc, 0, typed + l.addr, 16);
+        return;
+    }
+    if (l.rem == 8) {
+        // two 8-byte blocks: no shifts
+        const Loc32 l2 = at(rel + 8);
+        if (l2.rem >= 8) {
+            *gptr((u32x2a1 *)(typed + l.addr)) = u32x2a1{acc.w0, acc.w1};
+            *gptr((u32x2a1 *)(typed + l2.addr)) = u32x2a1{acc.w2, acc.w3};
+            return;
         }
-        // two runs split on a dword boundary, both dword aligned (blocks of
-        // float64 or int32 at a stride): four independent dword loads, each
-        // from whichever run holds that word
-        const uintptr_t a1 = (uintptr_t)(A.typed + l.addr);
-        const int t1 = (int)l.rem;
-        if (((a1 | (uintptr_t)t1) & 3) == 0) {
-            Loc l2 = locate<KIND>(L, (uint64_t)(A.off + lo + t1), A.elem1);
-            const uintptr_t a2 = (uintptr_t)(A.typed + l2.addr) - (uintptr_t)t1;  // chunk byte j of run 2 at a2 + j
-            if (l2.rem >= 16 - t1 && (a2 & 3) == 0) {
-                if (t1 == 8 && ((a1 | a2) & 7) == 0) {
-                    // two 8-byte blocks (float64 at a stride): one request each
-                    const u32x2 x = *gptr((const u32x2 *)a1);
-                    const u32x2 y = *gptr((const u32x2 *)(a2 + 8));
-                    acc = V4{x.x, x.y, y.x, y.y};
-                    return true;
-                }
-                acc.w0 = *gptr((const uint32_t *)(0 < t1 ? a1 : a2));
-                acc.w1 = *gptr((const uint32_t *)(4 < t1 ? a1 + 4 : a2 + 4));
-                acc.w2 = *gptr((const uint32_t *)(8 < t1 ? a1 + 8 : a2 + 8));
-                acc.w3 = *gptr((const uint32_t *)(12 < t1 ? a1 + 12 : a2 + 12));
-                return true;
+    }
+    scatter_runs(at, typed, rel, l, 0, 16, acc);
+}
+
+// the bytes of chunk k that the transfer's range holds
+__device__ __forceinline__ bool clipped_range(const Tile &T, int32_t k, int32_t &a, int32_t &b)
+{
+    const int32_t lo = T.r0 + 16 * k;
+    a = lo > 0 ? 0 : -lo;
+    b = lo + 16 < T.n ? 16 : T.n - lo;
+    return a < b;
+}
+
+template <class AT>
+__device__ __forceinline__ void pack_chunk(const AT &at, const XferArgs &A, const Tile &T, int32_t k)
+{
+    uint8_t *dst = T.chunk0 + 16 * k;
+    int32_t a, b;
+    if (!clipped_range(T, k, a, b)) return;
+    const V4 acc = gather_runs(at, A.typed, (uint32_t)(T.r0 + 16 * k + a), a, b - a);
+    if (b - a == 16) store_out(A, dst, u32x4{acc.w0, acc.w1, acc.w2, acc.w3});
+    else
+        for (int i = a; i < b; i++) gptr(dst)[i] = (uint8_t)byte_at(acc, i);
+}
+
+template <class AT>
+__device__ __forceinline__ void unpack_clipped(const AT &at, const XferArgs &A, const Tile &T, int32_t k)
+{
+    int32_t a, b;
+    if (!clipped_range(T, k, a, b)) return;
+    // the aligned 16-byte block holding this chunk's packed bytes
+    const u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)(T.chunk0 + 16 * k)));
+    const V4 acc = {v.x, v.y, v.z, v.w};
+    const uint32_t rel = (uint32_t)(T.r0 + 16 * k + a);
+    scatter_runs(at, const_cast<uint8_t *>(A.typed), rel, at(rel), a, b - a, acc);
+}
+
+// A lane's chunks lane + 256k (k < 4) of a tile, loads first: every chunk
+// whose 16 bytes lie in one run, or in two dword-aligned runs, is loaded
+// before any store is issued, so up to four gathers per lane are in flight
+// at once.  The other chunks then take the general body, one at a time.
+// ONE_RUN: the tile lies inside the run that starts at typed.
+// CACHED: the gathers load through the caches (a launch over runs shorter
+// than a line, whose lines other runs read soon after), else they stream.
+template <bool CACHED, class AT>
+__device__ __forceinline__ void pack_tile_at(const AT &at, const XferArgs &A, const Tile &T)
+{
+    const int32_t t = (int32_t)threadIdx.x;
+    const uint8_t *one = nullptr;  // the tile's first byte, when the whole tile lies in one run
+    if (at.run_may_hold((uint32_t)T.n)) {
+        const Loc32 l = at(0);
+        if (l.rem >= T.n) one = A.typed + l.addr;
+    }
+    V4 acc[4];
+    uint32_t fast = 0;
+    if (one && (((uintptr_t)one + (uintptr_t)T.r0) & 15) == 0) {
+        // an aligned copy: one test for the tile instead of one per load
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            int32_t rel;
+            if (T.whole(t + 256 * u, rel)) {
+                const u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)(one + rel)));
+                acc[u] = V4{v.x, v.y, v.z, v.w};
+                fast |= 1u << u;
             }
         }
+    } else if (one) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            int32_t rel;
+            if (T.whole(t + 256 * u, rel)) {
+                acc[u] = load16<false>(one + rel);
+                fast |= 1u << u;
+            }
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < 4; u++) {
+            int32_t rel;
+            if (T.whole(t + 256 * u, rel) && gather_fast<CACHED>(at, A.typed, (uint32_t)rel, acc[u])) fast |= 1u << u;
+        }
     }
-    return false;
-}
-
-__device__ __forceinline__ void store_chunk(const XferArgs &A, int64_t c, const V4 &acc)
-{
-    u32x4 v = {acc.w0, acc.w1, acc.w2, acc.w3};
-    store_out(A, (A.packed - A.head + 16 * c), v);
-}
-
-// Whole tile inside one run: the typed address of packed byte lo (relative
-// to the packed start) is base + lo.  Returns false when the tile's bytes
-// span several runs (or the layout is contiguous, which needs no test).
-template <int KIND>
-__device__ __forceinline__ bool tile_in_one_run(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t cend,
-                                                int64_t &base)
-{
-    const int64_t P_lo = max(16 * c0 - A.head, (int64_t)0);
-    const int64_t P_hi = min(16 * cend - A.head, A.nbytes);
-    Loc l = locate<KIND>(L, (uint64_t)(A.off + P_lo), A.elem1);
-    base = l.addr - P_lo;
-    return l.rem >= P_hi - P_lo;
-}
-
-template <int KIND>
-__device__ __forceinline__ void pack_tile_run(const XferArgs &A, int64_t c0, int64_t cend, int64_t base)
-{
-    const int64_t c = c0 + threadIdx.x;
-    V4 a0 = {0u, 0u, 0u, 0u}, a1 = a0, a2 = a0, a3 = a0;
-    uint32_t full = 0;
-#define MDT_RUN_LOAD(k, a)                                                   \
-    {                                                                        \
-        int64_t ck = c + 256 * (k), lo = 16 * ck - A.head;                   \
-        if (ck < cend && lo >= 0 && lo + 16 <= A.nbytes) {                   \
-            a = load16(A.typed + base + lo);                                 \
-            full |= 1u << (k);                                               \
-        }                                                                    \
-    }
-    MDT_RUN_LOAD(0, a0) MDT_RUN_LOAD(1, a1) MDT_RUN_LOAD(2, a2) MDT_RUN_LOAD(3, a3)
-#undef MDT_RUN_LOAD
-    if (full & 1u) store_chunk(A, c, a0);
-    if (full & 2u) store_chunk(A, c + 256, a1);
-    if (full & 4u) store_chunk(A, c + 512, a2);
-    if (full & 8u) store_chunk(A, c + 768, a3);
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+        if (fast & (1u << u))
+            store_out(A, T.chunk0 + 16 * (t + 256 * u), u32x4{acc[u].w0, acc[u].w1, acc[u].w2, acc[u].w3});
 #pragma unroll 1
-    for (int k = 0; k < 4; k++) {
-        int64_t ck = c + 256 * k;
-        if (ck >= cend || ((full >> k) & 1u)) continue;
-        // edge chunk of the transfer: byte by byte
-        const int64_t lo = 16 * ck - A.head;
-        const int64_t a = lo > 0 ? lo : 0, b = lo + 16 < A.nbytes ? lo + 16 : A.nbytes;
-        uint8_t *dst = A.packed - A.head + 16 * ck;
-        for (int64_t j = a; j < b; j++) gptr(dst)[j - lo] = gptr(A.typed)[base + j];
+    for (int u = 0; u < 4; u++) {
+        const int32_t k = t + 256 * u;
+        if (k < T.nc && !((fast >> u) & 1u)) pack_chunk(at, A, T, k);
     }
 }
 
-template <int KIND>
-__device__ __forceinline__ void unpack_tile_run(const XferArgs &A, int64_t c0, int64_t cend, int64_t base)
+// A lane's chunks lane + 256k (k < 4) of a tile: all four packed loads are
+// issued first, then each whole chunk is scattered from its loaded value
+// (stores only, so nothing waits between chunks).  Chunks clipped by the
+// transfer's range take the general body.
+template <class AT>
+__device__ __forceinline__ void unpack_tile_at(const AT &at, const XferArgs &A, const Tile &T)
 {
-    const int64_t c = c0 + threadIdx.x;
+    const int32_t t = (int32_t)threadIdx.x;
     uint8_t *typed = const_cast<uint8_t *>(A.typed);
-    V4 a0 = {0u, 0u, 0u, 0u}, a1 = a0, a2 = a0, a3 = a0;
-    uint32_t full = 0;
-#define MDT_RUN_LOAD(k, a)                                                               \
-    {                                                                                    \
-        int64_t ck = c + 256 * (k), lo = 16 * ck - A.head;                               \
-        if (ck < cend && lo >= 0 && lo + 16 <= A.nbytes) {                               \
-            u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)(A.packed - A.head + 16 * ck))); \
-            a = V4{v.x, v.y, v.z, v.w};                                                  \
-            full |= 1u << (k);                                                           \
-        }                                                                                \
+    uint8_t *one = nullptr;
+    if (at.run_may_hold((uint32_t)T.n)) {
+        const Loc32 l = at(0);
+        if (l.rem >= T.n) one = typed + l.addr;
     }
-    MDT_RUN_LOAD(0, a0) MDT_RUN_LOAD(1, a1) MDT_RUN_LOAD(2, a2) MDT_RUN_LOAD(3, a3)
-#undef MDT_RUN_LOAD
-    if (full & 1u) scatter(a0, 0, typed + base + (16 * c - A.head), 16);
-    if (full & 2u) scatter(a1, 0, typed + base + (16 * (c + 256) - A.head), 16);
-    if (full & 4u) scatter(a2, 0, typed + base + (16 * (c + 512) - A.head), 16);
-    if (full & 8u) scatter(a3, 0, typed + base + (16 * (c + 768) - A.head), 16);
+    V4 acc[4];
+    Loc32 loc[4];
+    uint32_t whole = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        int32_t rel;
+        if (T.whole(t + 256 * u, rel)) {
+            const u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)(T.chunk0 + 16 * (t + 256 * u))));
+            acc[u] = V4{v.x, v.y, v.z, v.w};
+            if (!one) loc[u] = at((uint32_t)rel);
+            whole |= 1u << u;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++)
+        if (whole & (1u << u)) {
+            const int32_t rel = T.r0 + 16 * (t + 256 * u);
+            if (one) scatter(acc[u], 0, one + rel, 16);
+            else scatter_chunk(at, typed, (uint32_t)rel, loc[u], acc[u]);
+        }
 #pragma unroll 1
-    for (int k = 0; k < 4; k++) {
-        int64_t ck = c + 256 * k;
-        if (ck >= cend || ((full >> k) & 1u)) continue;
-        const int64_t lo = 16 * ck - A.head;
-        const int64_t a = lo > 0 ? lo : 0, b = lo + 16 < A.nbytes ? lo + 16 : A.nbytes;
-        const uint8_t *src = A.packed - A.head + 16 * ck;
-        for (int64_t j = a; j < b; j++) gptr(typed)[base + j] = gptr(src)[j - lo];
+    for (int u = 0; u < 4; u++) {
+        const int32_t k = t + 256 * u;
+        if (k < T.nc && !((whole >> u) & 1u)) unpack_clipped(at, A, T, k);
     }
 }
 
-// A lane's chunks c0 + lane + 256k (k < 4) of a tile, loads first: every
-// chunk whose 16 bytes lie in one run, or in two dword-aligned runs, is
-// loaded before any store is issued, so up to four gathers per lane are in
-// flight at once.  The other chunks then take the general body, one at a
-// time.  A tile that lies inside one run is a plain copy.  CACHED: the
-// gathers load through the caches (a launch over runs shorter than a line,
-// whose lines other runs read soon after), else they stream.
+// Chunks [c0, cend) (at most 1024) of a transfer over layout L; KIND is the
+// transfer's kind (see xfer_kind).
 template <int KIND, bool CACHED = false>
 __device__ __forceinline__ void pack_tile4(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t cend)
 {
-    if (KIND != KIND_CONTIG) {
-        int64_t base;
-        if (tile_in_one_run<KIND>(L, A, c0, cend, base)) {
-            pack_tile_run<KIND>(A, c0, cend, base);
-            return;
-        }
-    }
-    const int64_t c = c0 + threadIdx.x;
-    V4 a0 = {0u, 0u, 0u, 0u}, a1 = a0, a2 = a0, a3 = a0;
-    uint32_t fast = (uint32_t)pack_first<KIND, CACHED>(L, A, c, cend, a0) |
-                    (uint32_t)pack_first<KIND, CACHED>(L, A, c + 256, cend, a1) << 1 |
-                    (uint32_t)pack_first<KIND, CACHED>(L, A, c + 512, cend, a2) << 2 |
-                    (uint32_t)pack_first<KIND, CACHED>(L, A, c + 768, cend, a3) << 3;
-    if (fast & 1u) store_chunk(A, c, a0);
-    if (fast & 2u) store_chunk(A, c + 256, a1);
-    if (fast & 4u) store_chunk(A, c + 512, a2);
-    if (fast & 8u) store_chunk(A, c + 768, a3);
-#pragma unroll 1
-    for (int k = 0; k < 4; k++) {
-        int64_t ck = c + 256 * k;
-        if (ck < cend && !((fast >> k) & 1u)) pack_chunk<KIND, CACHED>(L, A, ck);
-    }
+    const Tile T(A, c0, cend);
+    if constexpr (KIND == KIND_STRIDED) pack_tile_at<CACHED>(StridedAt<>(L.st, T.p0, A.elem1), A, T);
+    else pack_tile_at<CACHED>(GenericAt<KIND>(L, T.p0, A.elem1), A, T);
 }
 
-// Load chunk c's packed 16 bytes and locate its first byte; false for a
-// chunk outside the tile or one that the transfer's range clips.
-template <int KIND>
-__device__ __forceinline__ bool unpack_first(const DevLayout &L, const XferArgs &A, int64_t c, int64_t cend, V4 &acc,
-                                             Loc &loc)
-{
-    int64_t lo = 16 * c - A.head;
-    if (c < cend && lo >= 0 && lo + 16 <= A.nbytes) {
-        u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)(A.packed - A.head + 16 * c)));
-        acc = V4{v.x, v.y, v.z, v.w};
-        loc = locate<KIND>(L, (uint64_t)(A.off + lo), A.elem1);
-        return true;
-    }
-    return false;
-}
-
-// Store a whole chunk (stream bytes [p, p + 16), first run l) to the typed
-// side, run by run.  Stores do not wait, so a lane's chunks overlap.
-template <int KIND>
-__device__ __forceinline__ void scatter_chunk(const DevLayout &L, const XferArgs &A, uint64_t p, Loc l, const V4 &acc)
-{
-    uint8_t *dst = const_cast<uint8_t *>(A.typed);
-    if (l.rem >= 16) {
-        scatter(acc, 0, dst + l.addr, 16);
-        return;
-    }
-    int k = 0;
-    for (;;) {
-        int take = l.rem < 16 - k ? (int)l.rem : 16 - k;
-        if (take <= 0) break;  // unreachable for a well-formed layout; never spin
-        scatter(acc, k, dst + l.addr, take);
-        k += take;
-        if (k >= 16) break;
-        l = locate<KIND>(L, p + (uint64_t)k, A.elem1);
-    }
-}
-
-// A lane's chunks c0 + lane + 256k (k < 4) of a tile: all four packed loads
-// are issued first, then each whole chunk is scattered from its loaded value
-// (stores only, so nothing waits between chunks).  Chunks clipped by the
-// transfer's range take the general body.  A tile that lies inside one run
-// is a plain copy.
 template <int KIND>
 __device__ __forceinline__ void unpack_tile4(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t cend)
 {
-    if (KIND != KIND_CONTIG) {
-        int64_t base;
-        if (tile_in_one_run<KIND>(L, A, c0, cend, base)) {
-            unpack_tile_run<KIND>(A, c0, cend, base);
-            return;
-        }
-    }
-    const int64_t c = c0 + threadIdx.x;
-    V4 a0 = {0u, 0u, 0u, 0u}, a1 = a0, a2 = a0, a3 = a0;
-    Loc l0 = {0, 0}, l1 = l0, l2 = l0, l3 = l0;
-    uint32_t whole = (uint32_t)unpack_first<KIND>(L, A, c, cend, a0, l0) |
-                     (uint32_t)unpack_first<KIND>(L, A, c + 256, cend, a1, l1) << 1 |
-                     (uint32_t)unpack_first<KIND>(L, A, c + 512, cend, a2, l2) << 2 |
-                     (uint32_t)unpack_first<KIND>(L, A, c + 768, cend, a3, l3) << 3;
-    const uint64_t p = (uint64_t)(A.off + 16 * c - A.head);
-    if (whole & 1u) scatter_chunk<KIND>(L, A, p, l0, a0);
-    if (whole & 2u) scatter_chunk<KIND>(L, A, p + 4096, l1, a1);
-    if (whole & 4u) scatter_chunk<KIND>(L, A, p + 8192, l2, a2);
-    if (whole & 8u) scatter_chunk<KIND>(L, A, p + 12288, l3, a3);
-#pragma unroll 1
-    for (int k = 0; k < 4; k++) {
-        int64_t ck = c + 256 * k;
-        if (ck < cend && !((whole >> k) & 1u)) unpack_chunk<KIND>(L, A, ck);
-    }
+    const Tile T(A, c0, cend);
+    if constexpr (KIND == KIND_STRIDED) unpack_tile_at(StridedAt<>(L.st, T.p0, A.elem1), A, T);
+    else unpack_tile_at(GenericAt<KIND>(L, T.p0, A.elem1), A, T);
 }
-
-
 
 // ---------------------------------------------------------------------------
 // typed copy: a chunk of the stream gathered from one layout and scattered
