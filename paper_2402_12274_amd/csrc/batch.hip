@@ -713,6 +713,10 @@ int body_of(const DevLayout &L, const XferArgs &A, bool unpack, int32_t *lds)
         *lds = L.rec.lds_bytes;
         return BODY_DENSE;
     }
+    if (use_short_runs(L, A)) {
+        *lds = 16 * L.short_tile + 16;
+        return BODY_SHORT;
+    }
     if (use_runs(L)) {
         *lds = (int32_t)sizeof(RunsCache);
         return BODY_RUNS;

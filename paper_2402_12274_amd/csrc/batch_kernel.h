@@ -31,7 +31,8 @@ struct ReqDesc {
 constexpr int BODY_DENSE = 1;  // record view, LDS-staged
 constexpr int BODY_RUNS = 2;   // run tables, LDS-cached group slice
 constexpr int BODY_CHUNK = 4;  // chunk path
-constexpr int BODY_ALL = 7;
+constexpr int BODY_SHORT = 64; // tables of short runs, packed bytes in LDS
+constexpr int BODY_ALL = 7 | BODY_SHORT;
 constexpr int BODY_COPY = 8;   // typed copy (runs with the pack direction)
 constexpr int BODY_RELAY = 16; // pack, then unpack of the same packed bytes (runs with the pack direction)
 constexpr int BODY_CACHED = 32; // with BODY_CHUNK alone, pack: gathers load through the caches
@@ -112,6 +113,16 @@ __device__ __forceinline__ void run_tile(const DevLayout &L, const XferArgs &A, 
             int64_t s1 = s0 + 1024 < cend ? s0 + 1024 : cend;
             runs_tile<UNPACK != 0>(L, A, s0, s1, C);
             __syncthreads();  // the cache is refilled for the next sub-tile
+        }
+        return;
+    }
+    if ((BODY & BODY_SHORT) && body == BODY_SHORT) {
+        const RunsTab R = runs_tab(L);
+        const int64_t st = L.short_tile;
+        for (int64_t s0 = c0; s0 < cend; s0 += st) {
+            int64_t s1 = s0 + st < cend ? s0 + st : cend;
+            short_runs_tile<UNPACK != 0>(R, A, s0, s1, lds_dyn);
+            __syncthreads();
         }
         return;
     }
@@ -257,6 +268,7 @@ void launch_batch_dir_impl(dim3 grid, size_t lds, hipStream_t s, const BatchHead
     else if (!UNPACK && (body & BODY_COPY)) MDT_LAUNCH(UNPACK ? BODY_ALL : (BODY_ALL | BODY_COPY));
     else if (body == BODY_DENSE) MDT_LAUNCH(BODY_DENSE);
     else if (body == BODY_RUNS) MDT_LAUNCH(BODY_RUNS);
+    else if (body == BODY_SHORT) MDT_LAUNCH(BODY_SHORT);
     else if (!UNPACK && body == (BODY_CHUNK | BODY_CACHED)) MDT_LAUNCH(UNPACK ? BODY_ALL : (BODY_CHUNK | BODY_CACHED));
     else if (body == BODY_CHUNK) MDT_LAUNCH(BODY_CHUNK);
     else MDT_LAUNCH(BODY_ALL);

@@ -735,6 +735,16 @@ void lower(TypeNode *t, const Layout &L, Compiled &C)
         }
         D.nruns = orun;
         D.runs_only = L.outer.empty() && L.shapes.size() == 1 && L.shapes[0].varlen;
+        if (D.runs_only) {
+            // a lane moves its run alone, 16 bytes at a time: up to
+            // SHORT_RUN_MAX bytes and SHORT_RUN_MEAN on average that is
+            // better than searching each chunk's runs; a tile holds about
+            // as many runs as a workgroup has lanes
+            int64_t longest = 0;
+            for (const Group &gr : L.groups) longest = std::max(longest, gr.len);
+            if (longest <= SHORT_RUN_MAX && avg <= SHORT_RUN_MEAN)
+                D.short_tile = (int32_t)std::min<int64_t>(1024, std::max<int64_t>(64, 256 * avg / 16 / 64 * 64));
+        }
         D.gdisp = C.gdisp.data();
         D.gpre = C.gpre.data();
         D.grpre = C.grpre.data();

@@ -51,5 +51,9 @@ int64_t default_tile_chunks(int64_t nchunks);
 bool use_dense(const DevLayout &L, const XferArgs &A, bool unpack);
 // the run-table kernel (LDS-cached group slice) applies
 bool use_runs(const DevLayout &L);
+// of those, the kernel for short runs applies to this request
+bool use_short_runs(const DevLayout &L, const XferArgs &A);
+// chunks per tile for a kernel whose tiles hold at most `most`
+int64_t spread_tile(int64_t nchunks, int64_t most);
 
 }  // namespace mdt

@@ -246,6 +246,20 @@ __global__ __launch_bounds__(256) void runs_kernel(const DevLayout L, const Xfer
     }
 }
 
+// tables of short runs: the tile's packed bytes in LDS, one run per lane
+template <bool UNPACK>
+__global__ __launch_bounds__(256) void short_runs_kernel(const RunsTab R, const XferArgs A)
+{
+    extern __shared__ __align__(16) uint8_t lds_dyn[];
+    const int64_t ntiles = (A.nchunks + A.tile_chunks - 1) / A.tile_chunks;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        int64_t c0 = t * A.tile_chunks;
+        int64_t c1 = c0 + A.tile_chunks < A.nchunks ? c0 + A.tile_chunks : A.nchunks;
+        short_runs_tile<UNPACK>(R, A, c0, c1, lds_dyn);
+        __syncthreads();  // LDS is reused by the next tile
+    }
+}
+
 // flatten: one lane per segment
 __global__ __launch_bounds__(256) void flatten_kernel(const DevLayout L, int64_t off, int64_t m, mdt_iov *out,
                                                      uintptr_t base)
@@ -375,6 +389,19 @@ bool use_dense(const DevLayout &L, const XferArgs &A, bool unpack)
     return !unpack || R.unpack_ok;
 }
 
+// A transfer that fills fewer than two workgroups per CU with the largest
+// tiles gets smaller ones, down to a wavefront's worth of chunks.
+int64_t spread_tile(int64_t nchunks, int64_t most)
+{
+    return std::min(most, std::max<int64_t>(64, (nchunks / 512 + 63) / 64 * 64));
+}
+
+// Elements much smaller than a tile would leave most lanes idle.
+bool use_short_runs(const DevLayout &L, const XferArgs &A)
+{
+    return use_runs(L) && L.short_tile && (A.elem1 || L.size >= 4 * L.short_tile);
+}
+
 bool use_runs(const DevLayout &L) { return L.kind == KIND_MULTI && L.runs_only && runs_enabled(); }
 
 // the kernel compiled for the layout's number of levels
@@ -400,6 +427,15 @@ int launch_xfer(const DevLayout &L, const XferArgs &A0, bool unpack, hipStream_t
         size_t lds = (size_t)L.rec.lds_bytes;
         if (unpack) hipLaunchKernelGGL(dense_kernel<true>, dim3((unsigned)grid), dim3(256), lds, s, L, A);
         else hipLaunchKernelGGL(dense_kernel<false>, dim3((unsigned)grid), dim3(256), lds, s, L, A);
+        HIPCHK(hipGetLastError());
+        return MDT_SUCCESS;
+    }
+    if (use_short_runs(L, A)) {
+        A.tile_chunks = spread_tile(A.nchunks, L.short_tile);
+        int64_t grid = launch_grid((A.nchunks + A.tile_chunks - 1) / A.tile_chunks);
+        const size_t lds = 16 * (size_t)A.tile_chunks + 16;
+        if (unpack) hipLaunchKernelGGL(short_runs_kernel<true>, dim3((unsigned)grid), dim3(256), lds, s, runs_tab(L), A);
+        else hipLaunchKernelGGL(short_runs_kernel<false>, dim3((unsigned)grid), dim3(256), lds, s, runs_tab(L), A);
         HIPCHK(hipGetLastError());
         return MDT_SUCCESS;
     }

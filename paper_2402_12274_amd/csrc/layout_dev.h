@@ -180,6 +180,9 @@ struct DevRecords {
 constexpr int32_t REC_CTAB_MAX_U = 256;
 constexpr int32_t REC_DTAB_MAX_X = 1024;
 
+// Run tables whose runs are short (see DevLayout::short_tile).
+constexpr int64_t SHORT_RUN_MAX = 512, SHORT_RUN_MEAN = 128;
+
 // Compact program of a regular layout: one contiguous run under up to
 // STRIDED_MAX loops, positions and strides in 32 bits.  It is what the chunk
 // kernels locate with where it applies: a position takes one 32-bit
@@ -234,7 +237,7 @@ struct DevLayout {
     int32_t nshapes;
     int32_t dir_shift;      // directory granularity = 1 << dir_shift packed bytes
     int32_t runs_only;      // every group is a single run (varlen shape), no outer loops
-    int32_t pad1_;
+    int32_t short_tile;     // runs_only and every run short: chunks per tile of the short-run kernels, else 0
     int64_t ndir;           // directory entries
     const int64_t *gdisp;   // [G]   group displacement
     const int64_t *gpre;    // [G+1] packed-byte prefix of groups

@@ -1070,4 +1070,134 @@ __device__ __forceinline__ void runs_tile(const DevLayout &L, const XferArgs &A,
     }
 }
 
+// ---------------------------------------------------------------------------
+// tables of short runs: a workgroup takes the runs that meet its tile, one
+// per lane, straight from the group tables (the directory gives the first and
+// last group, so nothing is searched), and the tile's packed bytes pass
+// through LDS: pack gathers each run into its place there and the tile goes
+// out as whole chunks; unpack reads the tile as whole chunks and each lane
+// scatters its run from LDS.  Bound by the lines the runs touch: cold
+// scattered lines are read at 37-42 G/s, and partly written at 20-22 G/s.
+
+struct RunsTab {
+    const int64_t *gdisp, *gpre;
+    const int32_t *gdir;
+    int64_t size, extent, ndir, G;
+    MagicDiv dsize;
+    int32_t dir_shift;
+};
+
+MDT_HD RunsTab runs_tab(const DevLayout &L)
+{
+    return RunsTab{L.gdisp, L.gpre, L.gdir, L.size, L.extent, L.ndir, L.G, L.dsize, L.dir_shift};
+}
+
+// 16 bytes whose first n (0 < n < 16) are s[0..n), with one load that stays
+// inside the 128-byte lines that hold them: it ends at s + n where starting
+// at s would reach into the next line.
+__device__ __forceinline__ V4 load_short(const uint8_t *s, int n)
+{
+    const uint32_t back = ((uintptr_t)s & 127) > 112 ? (uint32_t)(16 - n) : 0u;
+    const unsigned __int128 v = as128(load16_any(s - back)) >> (8 * back);
+    return V4{(uint32_t)v, (uint32_t)(v >> 32), (uint32_t)(v >> 64), (uint32_t)(v >> 96)};
+}
+
+// the same bytes to LDS (any alignment; the piece's bytes only)
+__device__ __forceinline__ void lds_put16(uint8_t *d, const V4 &v) { *(u32x4a1 *)d = u32x4a1{v.w0, v.w1, v.w2, v.w3}; }
+
+__device__ __forceinline__ void lds_put_short(uint8_t *d, const V4 &a, int n)
+{
+    unsigned __int128 v = as128(a);
+    if (n & 8) {
+        *(u32x2a1 *)d = u32x2a1{(uint32_t)v, (uint32_t)(v >> 32)};
+        v >>= 64;
+        d += 8;
+    }
+    if (n & 4) {
+        *(u32a1 *)d = (uint32_t)v;
+        v >>= 32;
+        d += 4;
+    }
+    if (n & 2) {
+        *(u16a1 *)d = (uint16_t)v;
+        v >>= 16;
+        d += 2;
+    }
+    if (n & 1) *d = (uint8_t)v;
+}
+
+// Run s[0..n) to LDS at d.  A run of 16 bytes or more goes in 16-byte pieces
+// of which the last ends at its end (it may overlap the one before); the
+// first and the last are loaded together.
+__device__ __forceinline__ void run_to_lds(uint8_t *d, const uint8_t *s, int n)
+{
+    if (n < 16) {
+        lds_put_short(d, load_short(s, n), n);
+        return;
+    }
+    const V4 a = load16_any(s), z = load16_any(s + n - 16);
+    lds_put16(d, a);
+    lds_put16(d + n - 16, z);
+    for (int j = 16; j < n - 16; j += 16) lds_put16(d + j, load16_any(s + j));
+}
+
+__device__ __forceinline__ V4 lds_get16(const uint8_t *s)
+{
+    const u32x4a1 v = *(const u32x4a1 *)s;
+    return V4{v.x, v.y, v.z, v.w};
+}
+
+// LDS bytes s[0..n) to run d[0..n) (the 16 bytes at s are readable)
+__device__ __forceinline__ void run_from_lds(uint8_t *d, const uint8_t *s, int n)
+{
+    if (n < 16) {
+        scatter(lds_get16(s), 0, d, n);
+        return;
+    }
+    for (int j = 0; j < n - 16; j += 16) scatter(lds_get16(s + j), 0, d + j, 16);
+    scatter(lds_get16(s + n - 16), 0, d + n - 16, 16);
+}
+
+// Chunks [c0, c1) of a transfer; lds: 16 bytes per chunk and 16 more.
+template <bool UNPACK>
+__device__ __forceinline__ void short_runs_tile(const RunsTab &R, const XferArgs &A, int64_t c0, int64_t c1, uint8_t *lds)
+{
+    const Tile T(A, c0, c1);
+    if (UNPACK) {
+        for (int k = threadIdx.x; k < T.nc; k += blockDim.x)
+            *(u32x4 *)(lds + 16 * k) = __builtin_nontemporal_load(gptr((const u32x4 *)(T.chunk0 + 16 * k)));
+        __syncthreads();
+    }
+    // the tile's bytes in positions of its first element
+    const uint64_t e0 = A.elem1 ? 0 : magic_div(T.p0, R.dsize);
+    const int64_t pos0 = (int64_t)(T.p0 - e0 * (uint64_t)R.size), end = pos0 + T.n;
+    int64_t eaddr = (int64_t)e0 * R.extent;
+    for (int64_t q = 0; q < end; q += R.size, eaddr += R.extent) {
+        // bytes [s_lo, s_hi) of the element that starts at position q
+        const int64_t s_lo = max(pos0 - q, (int64_t)0), s_hi = min(end - q, R.size);
+        const int64_t k1 = (s_hi - 1) >> R.dir_shift;
+        const int64_t g0 = gld(R.gdir, s_lo >> R.dir_shift);
+        const int64_t g1 = k1 + 1 < R.ndir ? (int64_t)gld(R.gdir, k1 + 1) : R.G - 1;
+        const int64_t to_lds = q - pos0 - T.r0;
+        for (int64_t g = g0 + threadIdx.x; g <= g1; g += blockDim.x) {
+            const int64_t pre = gld(R.gpre, g), nxt = gld(R.gpre, g + 1), disp = gld(R.gdisp, g);
+            const int64_t a = max(pre, s_lo), b = min(nxt, s_hi);
+            if (a >= b) continue;  // a group of the directory's cells outside the tile
+            uint8_t *typed = const_cast<uint8_t *>(A.typed) + (eaddr + disp + (a - pre));
+            uint8_t *at = lds + (uint32_t)(a + to_lds);
+            if (UNPACK) run_from_lds(typed, at, (int)(b - a));
+            else run_to_lds(at, typed, (int)(b - a));
+        }
+    }
+    if (UNPACK) return;
+    __syncthreads();
+    for (int k = threadIdx.x; k < T.nc; k += blockDim.x) {
+        int32_t a, b;
+        if (!clipped_range(T, k, a, b)) continue;
+        if (b - a == 16) store_out(A, T.chunk0 + 16 * k, *(const u32x4 *)(lds + 16 * k));
+        else
+            for (int i = a; i < b; i++) gptr(T.chunk0)[16 * k + i] = lds[16 * k + i];
+    }
+}
+
 }  // namespace mdt
