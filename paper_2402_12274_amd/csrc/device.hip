@@ -283,6 +283,17 @@ __global__ __launch_bounds__(256) void flatten_table_kernel(const mdt_iov *segs,
 
 // flatten over count consecutive elements: lane i writes segment off + i of
 // the count form (the element's segments repeated at multiples of the
+// run tables: segment k is group k
+__global__ __launch_bounds__(256) void flatten_runs_kernel(const int64_t *gdisp, const int64_t *gpre, int64_t m,
+                                                          mdt_iov *out, uintptr_t base)
+{
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= m) return;
+    const int64_t a = gld(gdisp, i), p0 = gld(gpre, i), p1 = gld(gpre, i + 1);
+    out[i].iov_base = (void *)(base + (uintptr_t)a);
+    out[i].iov_len = p1 - p0;
+}
+
 // extent; with `merge`, each element's last segment joined to the next
 // element's first).  TABLE: segments come from the merged-segment table,
 // else from the layout's runs.
@@ -531,6 +542,9 @@ int launch_flatten(Compiled *c, DeviceTables *d, int64_t off, int64_t m, mdt_iov
             HIPCHK(hipMemcpy(p, h.data(), n * sizeof(mdt_iov), hipMemcpyHostToDevice));
             d->d_segs = (mdt_iov *)p;
         }
+        else if (d->lay.runs_only)
+            hipLaunchKernelGGL(flatten_runs_kernel, g, b, 0, s, d->lay.gdisp + off, d->lay.gpre + off, m, out,
+                               (uintptr_t)base);
         if (counted)
             hipLaunchKernelGGL(flatten_count_kernel<true>, g, b, 0, s, d->lay, (const mdt_iov *)d->d_segs, sc->n,
                                (int)sc->merge, sc->count, sc->extent, off, m, out, (uintptr_t)base);

@@ -493,7 +493,8 @@ MDT_HD RunInfo run_at(const DevLayout &L, uint64_t k)
                 addr += (int64_t)i * L.ostride[l];
             }
         }
-        int64_t lo = 0, hi = L.G - 1;
+        // with one run in every group, run k is in group k
+        int64_t lo = L.gruns == L.G ? (int64_t)k : 0, hi = L.gruns == L.G ? (int64_t)k : L.G - 1;
         while (lo < hi) {
             int64_t mid = (lo + hi + 1) >> 1;
             if ((uint64_t)gld(L.grpre, mid) <= k) lo = mid; else hi = mid - 1;
