@@ -219,7 +219,7 @@ __global__ __launch_bounds__(256) void copy_kernel(const DevLayout Ls, const Dev
 
 // dense record streams: one tile of chunks per workgroup, staged in LDS
 template <bool UNPACK>
-__global__ __launch_bounds__(256) void dense_kernel(const DevLayout L, const XferArgs A)
+__global__ __launch_bounds__(256) void dense_kernel(const RecordsOnly L, const XferArgs A)
 {
     extern __shared__ __align__(16) uint8_t lds_dyn[];
     const int64_t ntiles = (A.nchunks + A.tile_chunks - 1) / A.tile_chunks;
@@ -433,11 +433,11 @@ int launch_xfer(const DevLayout &L, const XferArgs &A0, bool unpack, hipStream_t
     A.elem1 = A.off + A.nbytes <= L.size;
     A.keep = !unpack && A.nbytes <= KEEP_PACKED_MAX;
     if (use_dense(L, A, unpack)) {
-        A.tile_chunks = L.rec.tile_chunks;
+        A.tile_chunks = spread_tile(A.nchunks, L.rec.tile_chunks);
         int64_t grid = launch_grid((A.nchunks + A.tile_chunks - 1) / A.tile_chunks);
         size_t lds = (size_t)L.rec.lds_bytes;
-        if (unpack) hipLaunchKernelGGL(dense_kernel<true>, dim3((unsigned)grid), dim3(256), lds, s, L, A);
-        else hipLaunchKernelGGL(dense_kernel<false>, dim3((unsigned)grid), dim3(256), lds, s, L, A);
+        if (unpack) hipLaunchKernelGGL(dense_kernel<true>, dim3((unsigned)grid), dim3(256), lds, s, RecordsOnly{L.rec}, A);
+        else hipLaunchKernelGGL(dense_kernel<false>, dim3((unsigned)grid), dim3(256), lds, s, RecordsOnly{L.rec}, A);
         HIPCHK(hipGetLastError());
         return MDT_SUCCESS;
     }

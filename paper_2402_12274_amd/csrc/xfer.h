@@ -646,11 +646,18 @@ __device__ __forceinline__ uint32_t dense_word(const uint32_t *tab, const uint8_
     return v;
 }
 
-// Pack chunks [c0, c1) of A (a tile) with the record view of L and its byte
+// Pack chunks [c0, c1) of A (a tile) with the record view and its byte
 // table.  `lds` holds rec.lds_bytes of dynamic shared memory.
-__device__ __forceinline__ void dense_pack_tile_b(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t c1,
+template <class LAY>
+__device__ __forceinline__ void dense_pack_tile_b(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                 uint8_t *lds)
 {
+// A record view without the rest of its layout, as a kernel argument (the
+// tile bodies below take anything with a member `rec`).
+struct RecordsOnly {
+    DevRecords rec;
+};
+
     const DevRecords &R = L.rec;
     const int64_t P_lo = max(16 * c0 - A.head, (int64_t)0);
     const int64_t P_hi = min(16 * c1 - A.head, A.nbytes);
@@ -695,7 +702,8 @@ __device__ __forceinline__ void dense_pack_tile_b(const DevLayout &L, const Xfer
 // Unpack chunks [c0, c1) of A (a tile) with the byte table: the packed tile
 // goes to LDS, then the lanes walk the typed span dword by dword and store
 // the typemap bytes that belong to this tile.
-__device__ __forceinline__ void dense_unpack_tile_b(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t c1,
+template <class LAY>
+__device__ __forceinline__ void dense_unpack_tile_b(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                   uint8_t *lds)
 {
     const DevRecords &R = L.rec;
@@ -760,7 +768,8 @@ __device__ __forceinline__ uint32_t lds_gather4(const uint8_t *lds, uint32_t rb,
 // finds the record and phase of its first byte, the table entry of that
 // phase gives the 16 typed offsets, and the bytes are gathered from the
 // staged span.  Only the two edge chunks of a transfer go byte by byte.
-__device__ __forceinline__ void dense_pack_tile_c(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t c1,
+template <class LAY>
+__device__ __forceinline__ void dense_pack_tile_c(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                   uint8_t *lds)
 {
     const DevRecords &R = L.rec;
@@ -812,7 +821,8 @@ __device__ __forceinline__ void dense_pack_tile_c(const DevLayout &L, const Xfer
 // whole: a dword shared with a neighbouring tile is written by both with the
 // same bytes.  Away from the transfer's ends nothing is clipped and no byte
 // needs a range test; gap bytes are never written.
-__device__ __forceinline__ void dense_unpack_tile_d(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t c1,
+template <class LAY>
+__device__ __forceinline__ void dense_unpack_tile_d(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                     uint8_t *lds)
 {
     const DevRecords &R = L.rec;
@@ -874,14 +884,16 @@ __device__ __forceinline__ void dense_unpack_tile_d(const DevLayout &L, const Xf
     }
 }
 
-__device__ __forceinline__ void dense_pack_tile(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t c1,
+template <class LAY>
+__device__ __forceinline__ void dense_pack_tile(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                 uint8_t *lds)
 {
     if (L.rec.ctab) dense_pack_tile_c(L, A, c0, c1, lds);
     else dense_pack_tile_b(L, A, c0, c1, lds);
 }
 
-__device__ __forceinline__ void dense_unpack_tile(const DevLayout &L, const XferArgs &A, int64_t c0, int64_t c1,
+template <class LAY>
+__device__ __forceinline__ void dense_unpack_tile(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                   uint8_t *lds)
 {
     if (L.rec.dtab) dense_unpack_tile_d(L, A, c0, c1, lds);
