@@ -36,6 +36,7 @@ struct CopyArgs {
     int64_t off;           // first stream position copied
     int64_t nbytes;        // bytes copied
     int64_t nchunks;       // ceil(nbytes / 16)
+    int64_t tile_chunks;   // chunks per workgroup tile (set at launch)
     int32_t src_elem1;     // off + nbytes <= source element size
     int32_t dst_elem1;     // off + nbytes <= destination element size
 };

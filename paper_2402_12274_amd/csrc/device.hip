@@ -205,15 +205,27 @@ __global__ __launch_bounds__(256) void strided_kernel(const DevStrided S, const 
     }
 }
 
-// typed copy: one tile of 1024 chunks per workgroup (four per lane)
+// typed copy: one tile of A.tile_chunks chunks per workgroup (at most four
+// per lane)
 template <int KS, int KD>
 __global__ __launch_bounds__(256) void copy_kernel(const DevLayout Ls, const DevLayout Ld, const CopyArgs A)
 {
-    const int64_t ntiles = (A.nchunks + 1023) / 1024;
+    const int64_t ntiles = (A.nchunks + A.tile_chunks - 1) / A.tile_chunks;
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int64_t c0 = t * 1024;
-        const int64_t cend = c0 + 1024 < A.nchunks ? c0 + 1024 : A.nchunks;
+        const int64_t c0 = t * A.tile_chunks;
+        const int64_t cend = c0 + A.tile_chunks < A.nchunks ? c0 + A.tile_chunks : A.nchunks;
         copy_tile4<KS, KD>(Ls, Ld, A, c0, cend);
+    }
+}
+
+// the same between two regular layouts
+__global__ __launch_bounds__(256) void copy_strided_kernel(const DevStrided Ss, const DevStrided Sd, const CopyArgs A)
+{
+    const int64_t ntiles = (A.nchunks + A.tile_chunks - 1) / A.tile_chunks;
+    for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        const int64_t c0 = t * A.tile_chunks;
+        const int64_t cend = c0 + A.tile_chunks < A.nchunks ? c0 + A.tile_chunks : A.nchunks;
+        copy_tile_strided(Ss, Sd, A, c0, cend);
     }
 }
 
@@ -271,6 +283,17 @@ __global__ __launch_bounds__(256) void flatten_kernel(const DevLayout L, int64_t
     out[i].iov_len = r.len;
 }
 
+// run tables: segment k is group k
+__global__ __launch_bounds__(256) void flatten_runs_kernel(const int64_t *gdisp, const int64_t *gpre, int64_t m,
+                                                          mdt_iov *out, uintptr_t base)
+{
+    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= m) return;
+    const int64_t a = gld(gdisp, i), p0 = gld(gpre, i), p1 = gld(gpre, i + 1);
+    out[i].iov_base = (void *)(base + (uintptr_t)a);
+    out[i].iov_len = p1 - p0;
+}
+
 __global__ __launch_bounds__(256) void flatten_table_kernel(const mdt_iov *segs, int64_t off, int64_t m,
                                                            mdt_iov *out, uintptr_t base)
 {
@@ -283,17 +306,6 @@ __global__ __launch_bounds__(256) void flatten_table_kernel(const mdt_iov *segs,
 
 // flatten over count consecutive elements: lane i writes segment off + i of
 // the count form (the element's segments repeated at multiples of the
-// run tables: segment k is group k
-__global__ __launch_bounds__(256) void flatten_runs_kernel(const int64_t *gdisp, const int64_t *gpre, int64_t m,
-                                                          mdt_iov *out, uintptr_t base)
-{
-    int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= m) return;
-    const int64_t a = gld(gdisp, i), p0 = gld(gpre, i), p1 = gld(gpre, i + 1);
-    out[i].iov_base = (void *)(base + (uintptr_t)a);
-    out[i].iov_len = p1 - p0;
-}
-
 // extent; with `merge`, each element's last segment joined to the next
 // element's first).  TABLE: segments come from the merged-segment table,
 // else from the layout's runs.
@@ -481,21 +493,26 @@ int launch_xfer(const DevLayout &L, const XferArgs &A0, bool unpack, hipStream_t
     return MDT_SUCCESS;
 }
 
-template <int KS>
-static void launch_copy_kd(const DevLayout &Ls, const DevLayout &Ld, const CopyArgs &A, dim3 g, hipStream_t s)
+int launch_copy(const DevLayout &Ls, const DevLayout &Ld, const CopyArgs &A0, hipStream_t s)
 {
-    if (Ld.kind == KIND_CONTIG) hipLaunchKernelGGL((copy_kernel<KS, KIND_CONTIG>), g, dim3(256), 0, s, Ls, Ld, A);
-    else if (Ld.kind == KIND_SINGLE) hipLaunchKernelGGL((copy_kernel<KS, KIND_SINGLE>), g, dim3(256), 0, s, Ls, Ld, A);
-    else hipLaunchKernelGGL((copy_kernel<KS, KIND_MULTI>), g, dim3(256), 0, s, Ls, Ld, A);
-}
-
-int launch_copy(const DevLayout &Ls, const DevLayout &Ld, const CopyArgs &A, hipStream_t s)
-{
-    if (A.nbytes == 0 || Ls.kind == KIND_EMPTY || Ld.kind == KIND_EMPTY) return MDT_SUCCESS;
-    const dim3 g((unsigned)launch_grid((A.nchunks + 1023) / 1024));
-    if (Ls.kind == KIND_CONTIG) launch_copy_kd<KIND_CONTIG>(Ls, Ld, A, g, s);
-    else if (Ls.kind == KIND_SINGLE) launch_copy_kd<KIND_SINGLE>(Ls, Ld, A, g, s);
-    else launch_copy_kd<KIND_MULTI>(Ls, Ld, A, g, s);
+    if (A0.nbytes == 0 || Ls.kind == KIND_EMPTY || Ld.kind == KIND_EMPTY) return MDT_SUCCESS;
+    // with one side contiguous the copy is a pack into it, or an unpack from
+    // it, and takes their kernels
+    if (Ld.kind == KIND_CONTIG)
+        return launch_xfer(Ls, make_args(A0.src, A0.dst + (Ld.gdisp0 + A0.off), A0.off, A0.nbytes), false, s);
+    if (Ls.kind == KIND_CONTIG)
+        return launch_xfer(Ld, make_args(A0.dst, const_cast<uint8_t *>(A0.src) + (Ls.gdisp0 + A0.off), A0.off, A0.nbytes),
+                           true, s);
+    CopyArgs A = A0;
+    A.tile_chunks = default_tile_chunks(A.nchunks);
+    const dim3 g((unsigned)launch_grid((A.nchunks + A.tile_chunks - 1) / A.tile_chunks));
+    if (xfer_kind(Ls, A.src_elem1) == KIND_STRIDED && xfer_kind(Ld, A.dst_elem1) == KIND_STRIDED)
+        hipLaunchKernelGGL(copy_strided_kernel, g, dim3(256), 0, s, Ls.st, Ld.st, A);
+    else if (Ls.kind == KIND_SINGLE && Ld.kind == KIND_SINGLE)
+        hipLaunchKernelGGL((copy_kernel<KIND_SINGLE, KIND_SINGLE>), g, dim3(256), 0, s, Ls, Ld, A);
+    else if (Ls.kind == KIND_SINGLE) hipLaunchKernelGGL((copy_kernel<KIND_SINGLE, KIND_MULTI>), g, dim3(256), 0, s, Ls, Ld, A);
+    else if (Ld.kind == KIND_SINGLE) hipLaunchKernelGGL((copy_kernel<KIND_MULTI, KIND_SINGLE>), g, dim3(256), 0, s, Ls, Ld, A);
+    else hipLaunchKernelGGL((copy_kernel<KIND_MULTI, KIND_MULTI>), g, dim3(256), 0, s, Ls, Ld, A);
     HIPCHK(hipGetLastError());
     return MDT_SUCCESS;
 }
@@ -525,6 +542,9 @@ int launch_flatten(Compiled *c, DeviceTables *d, int64_t off, int64_t m, mdt_iov
         if (counted)
             hipLaunchKernelGGL(flatten_count_kernel<false>, g, b, 0, s, d->lay, (const mdt_iov *)nullptr, sc->n,
                                (int)sc->merge, sc->count, sc->extent, off, m, out, (uintptr_t)base);
+        else if (d->lay.runs_only)
+            hipLaunchKernelGGL(flatten_runs_kernel, g, b, 0, s, d->lay.gdisp + off, d->lay.gpre + off, m, out,
+                               (uintptr_t)base);
         else
             hipLaunchKernelGGL(flatten_kernel, g, b, 0, s, d->lay, off, m, out, (uintptr_t)base);
     } else {
@@ -542,9 +562,6 @@ int launch_flatten(Compiled *c, DeviceTables *d, int64_t off, int64_t m, mdt_iov
             HIPCHK(hipMemcpy(p, h.data(), n * sizeof(mdt_iov), hipMemcpyHostToDevice));
             d->d_segs = (mdt_iov *)p;
         }
-        else if (d->lay.runs_only)
-            hipLaunchKernelGGL(flatten_runs_kernel, g, b, 0, s, d->lay.gdisp + off, d->lay.gpre + off, m, out,
-                               (uintptr_t)base);
         if (counted)
             hipLaunchKernelGGL(flatten_count_kernel<true>, g, b, 0, s, d->lay, (const mdt_iov *)d->d_segs, sc->n,
                                (int)sc->merge, sc->count, sc->extent, off, m, out, (uintptr_t)base);

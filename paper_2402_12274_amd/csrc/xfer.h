@@ -584,6 +584,38 @@ __device__ __forceinline__ void copy_tile4(const DevLayout &Ls, const DevLayout 
 #undef MDT_COPY_P
 }
 
+// The same between two regular layouts: whole chunks of one or two source
+// runs are loaded first, all of them, then scattered; the others follow one
+// at a time.  (Single launches only: the batch kernels, which carry every
+// pair of kinds, take the compiler many minutes with this body added.)
+__device__ __forceinline__ void copy_tile_strided(const DevStrided &Ss, const DevStrided &Sd, const CopyArgs &A,
+                                                  int64_t c0, int64_t cend)
+{
+    const uint64_t p0 = (uint64_t)(A.off + 16 * c0);
+    const StridedAt<> sa(Ss, p0, A.src_elem1), da(Sd, p0, A.dst_elem1);
+    const int32_t t = (int32_t)threadIdx.x, nc = (int32_t)(cend - c0);
+    const int32_t n = (int32_t)min(16 * (cend - c0), A.nbytes - 16 * c0);
+    V4 acc[4];
+    uint32_t fast = 0;
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int32_t rel = 16 * (t + 256 * u);
+        if (rel + 16 <= n && gather_fast<true>(sa, A.src, (uint32_t)rel, acc[u])) fast |= 1u << u;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const uint32_t rel = 16 * (uint32_t)(t + 256 * u);
+        if (fast & (1u << u)) scatter_chunk(da, A.dst, rel, da(rel), acc[u]);
+    }
+#pragma unroll 1
+    for (int u = 0; u < 4; u++) {
+        const int32_t k = t + 256 * u, rel = 16 * k;
+        if (k >= nc || ((fast >> u) & 1u)) continue;
+        const int m = rel + 16 <= n ? 16 : n - rel;
+        scatter_runs(da, A.dst, (uint32_t)rel, da((uint32_t)rel), 0, m, gather_runs(sa, A.src, (uint32_t)rel, 0, m));
+    }
+}
+
 }  // namespace mdt
 
 namespace mdt {
@@ -619,6 +651,12 @@ __device__ __forceinline__ uint32_t stage_span(uint8_t *lds, const uint8_t *g_lo
     return (uint32_t)((uintptr_t)g_lo - a);
 }
 
+// A record view without the rest of its layout, as a kernel argument (the
+// tile bodies below take anything with a member `rec`).
+struct RecordsOnly {
+    DevRecords rec;
+};
+
 // Next packed word of a dense record stream: q is the packed offset inside
 // record er (relative to the tile's first record); both advance by 4.
 __device__ __forceinline__ uint32_t dense_word(const uint32_t *tab, const uint8_t *span, uint32_t base, uint32_t X,
@@ -652,12 +690,6 @@ template <class LAY>
 __device__ __forceinline__ void dense_pack_tile_b(const LAY &L, const XferArgs &A, int64_t c0, int64_t c1,
                                                 uint8_t *lds)
 {
-// A record view without the rest of its layout, as a kernel argument (the
-// tile bodies below take anything with a member `rec`).
-struct RecordsOnly {
-    DevRecords rec;
-};
-
     const DevRecords &R = L.rec;
     const int64_t P_lo = max(16 * c0 - A.head, (int64_t)0);
     const int64_t P_hi = min(16 * c1 - A.head, A.nbytes);
