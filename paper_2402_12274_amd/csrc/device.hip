@@ -205,7 +205,12 @@ __global__ __launch_bounds__(256) void strided_kernel(const DevStrided S, const 
     }
 }
 
-// typed copy: one tile of A.tile_chunks chunks per workgroup (at most four
+// Typed copies.  Between regular layouts the copy_strided_kernel below is
+// bound by the scattered lines of both sides: the twelve ghost-layer copies
+// of a 512^3 array took 243 us through the general program (a chunk located
+// by 64-bit divisions on each side, gathered word by word, a 2 MB face in 127
+// workgroups) and take 110-119 us through the compact one.
+// General form: one tile of A.tile_chunks chunks per workgroup (at most four
 // per lane)
 template <int KS, int KD>
 __global__ __launch_bounds__(256) void copy_kernel(const DevLayout Ls, const DevLayout Ld, const CopyArgs A)
@@ -258,7 +263,9 @@ __global__ __launch_bounds__(256) void runs_kernel(const DevLayout L, const Xfer
     }
 }
 
-// tables of short runs: the tile's packed bytes in LDS, one run per lane
+// tables of short runs: the tile's packed bytes in LDS, one run per lane (1M
+// blocks of 24 bytes: pack 82.7 -> 63.4 us, unpack 56.5 -> 51.0 us against a
+// search of each chunk's runs; the line rates put them at 36 and 50)
 template <bool UNPACK>
 __global__ __launch_bounds__(256) void short_runs_kernel(const RunsTab R, const XferArgs A)
 {
@@ -283,7 +290,8 @@ __global__ __launch_bounds__(256) void flatten_kernel(const DevLayout L, int64_t
     out[i].iov_len = r.len;
 }
 
-// run tables: segment k is group k
+// run tables: segment k is group k (1M blocks: 6 us, bound by the 16 MB read
+// and 16 MB written; 23 us with a search per segment)
 __global__ __launch_bounds__(256) void flatten_runs_kernel(const int64_t *gdisp, const int64_t *gpre, int64_t m,
                                                           mdt_iov *out, uintptr_t base)
 {
@@ -413,7 +421,8 @@ bool use_dense(const DevLayout &L, const XferArgs &A, bool unpack)
 }
 
 // A transfer that fills fewer than two workgroups per CU with the largest
-// tiles gets smaller ones, down to a wavefront's worth of chunks.
+// tiles gets smaller ones, down to a wavefront's worth of chunks (64 ranges
+// of 1 MiB of records: 503 us in 64 workgroups each, 295 us in 512).
 int64_t spread_tile(int64_t nchunks, int64_t most)
 {
     return std::min(most, std::max<int64_t>(64, (nchunks / 512 + 63) / 64 * 64));
