@@ -333,7 +333,8 @@ __device__ __forceinline__ bool gather_fast(const AT &at, const uint8_t *typed, 
 }
 
 // Chunk bytes [k, k + n) to the typed bytes from `rel` on, run by run (l:
-// the first run).  Stores do not wait, so a lane's chunks overlap.
+// the first run).  Stores do not wait, so a lane's chunks overlap.  An
+// aligned half of the chunk (float64 blocks) goes out without the shifts.
 template <class AT>
 __device__ __forceinline__ void scatter_runs(const AT &at, uint8_t *typed, uint32_t rel, Loc32 l, int k, int n,
                                              const V4 &acc)
@@ -342,31 +343,25 @@ __device__ __forceinline__ void scatter_runs(const AT &at, uint8_t *typed, uint3
     for (;;) {
         const int t = l.rem < n - done ? l.rem : n - done;
         if (t <= 0) break;  // unreachable for a well-formed layout; never spin
-        scatter(acc, k + done, typed + l.addr, t);
+        const int at0 = k + done;
+        if (t == 8 && (at0 & 7) == 0)
+            *gptr((u32x2a1 *)(typed + l.addr)) = at0 ? u32x2a1{acc.w2, acc.w3} : u32x2a1{acc.w0, acc.w1};
+        else
+            scatter(acc, at0, typed + l.addr, t);
         done += t;
         if (done >= n) break;
         l = at(rel + (uint32_t)done);
     }
 }
 
-// Store a whole chunk to the typed side.
+// Store a whole chunk, whose first byte is byte `rel` of the tile, to the
+// typed side.
 template <class AT>
-__device__ __forceinline__ void scatter_chunk(const AT &at, uint8_t *typed, uint32_t rel, const Loc32 &l, const V4 &acc)
+__device__ __forceinline__ void scatter_chunk(const AT &at, uint8_t *typed, uint32_t rel, const V4 &acc)
 {
-    if (l.rem >= 16) {
-        scatter(acc, 0, typed + l.addr, 16);
-        return;
-    }
-    if (l.rem == 8) {
-        // two 8-byte blocks: no shifts
-        const Loc32 l2 = at(rel + 8);
-        if (l2.rem >= 8) {
-            *gptr((u32x2a1 *)(typed + l.addr)) = u32x2a1{acc.w0, acc.w1};
-            *gptr((u32x2a1 *)(typed + l2.addr)) = u32x2a1{acc.w2, acc.w3};
-            return;
-        }
-    }
-    scatter_runs(at, typed, rel, l, 0, 16, acc);
+    const Loc32 l = at(rel);
+    if (l.rem >= 16) scatter(acc, 0, typed + l.addr, 16);
+    else scatter_runs(at, typed, rel, l, 0, 16, acc);
 }
 
 // the bytes of chunk k that the transfer's range holds
@@ -459,9 +454,14 @@ __device__ __forceinline__ void pack_tile_at(const AT &at, const XferArgs &A, co
 }
 
 // A lane's chunks lane + 256k (k < 4) of a tile: all four packed loads are
-// issued first, then each whole chunk is scattered from its loaded value
-// (stores only, so nothing waits between chunks).  Chunks clipped by the
-// transfer's range take the general body.
+// issued first, then each whole chunk is located and scattered from its
+// loaded value (stores only, so nothing waits between chunks).  Chunks
+// clipped by the transfer's range take the general body.  Latency is hidden
+// by waves here, so registers decide: with the four locations held over the
+// loads, and two 8-byte blocks in a form of their own beside the loop over
+// runs, the batch kernel of every body took 155 of them (three waves per
+// SIMD) where it takes 77 (six), and 136 mixed unpacks of up to 4 MiB 166 us
+// where they take 125.
 template <class AT>
 __device__ __forceinline__ void unpack_tile_at(const AT &at, const XferArgs &A, const Tile &T)
 {
@@ -473,7 +473,6 @@ __device__ __forceinline__ void unpack_tile_at(const AT &at, const XferArgs &A, 
         if (l.rem >= T.n) one = typed + l.addr;
     }
     V4 acc[4];
-    Loc32 loc[4];
     uint32_t whole = 0;
 #pragma unroll
     for (int u = 0; u < 4; u++) {
@@ -481,7 +480,6 @@ __device__ __forceinline__ void unpack_tile_at(const AT &at, const XferArgs &A, 
         if (T.whole(t + 256 * u, rel)) {
             const u32x4 v = __builtin_nontemporal_load(gptr((const u32x4 *)(T.chunk0 + 16 * (t + 256 * u))));
             acc[u] = V4{v.x, v.y, v.z, v.w};
-            if (!one) loc[u] = at((uint32_t)rel);
             whole |= 1u << u;
         }
     }
@@ -490,7 +488,7 @@ __device__ __forceinline__ void unpack_tile_at(const AT &at, const XferArgs &A, 
         if (whole & (1u << u)) {
             const int32_t rel = T.r0 + 16 * (t + 256 * u);
             if (one) scatter(acc[u], 0, one + rel, 16);
-            else scatter_chunk(at, typed, (uint32_t)rel, loc[u], acc[u]);
+            else scatter_chunk(at, typed, (uint32_t)rel, acc[u]);
         }
 #pragma unroll 1
     for (int u = 0; u < 4; u++) {
@@ -605,7 +603,7 @@ __device__ __forceinline__ void copy_tile_strided(const DevStrided &Ss, const De
 #pragma unroll
     for (int u = 0; u < 4; u++) {
         const uint32_t rel = 16 * (uint32_t)(t + 256 * u);
-        if (fast & (1u << u)) scatter_chunk(da, A.dst, rel, da(rel), acc[u]);
+        if (fast & (1u << u)) scatter_chunk(da, A.dst, rel, acc[u]);
     }
 #pragma unroll 1
     for (int u = 0; u < 4; u++) {
