@@ -54,22 +54,14 @@ __device__ __forceinline__ void store_out(const XferArgs &A, uint8_t *dst, const
     else __builtin_nontemporal_store(v, gptr((u32x4 *)dst));
 }
 
-// Byte / dword extraction at a variable byte position of the chunk, as
-// 128-bit shifts (funnel shifts in registers; an indexed select would be
-// turned into a per-lane memory array).
+// A chunk as one 128-bit value, for shifts by a variable number of bytes
+// (funnel shifts in registers; an indexed select would be turned into a
+// per-lane memory array).
 __device__ __forceinline__ unsigned __int128 as128(const V4 &a)
 {
     return ((unsigned __int128)a.w3 << 96) | ((unsigned __int128)a.w2 << 64) | ((unsigned __int128)a.w1 << 32) |
            (unsigned __int128)a.w0;
 }
-
-__device__ __forceinline__ uint32_t byte_at(const V4 &a, int pos)
-{
-    return (uint32_t)(as128(a) >> (8 * pos)) & 0xffu;
-}
-
-// 4 bytes starting at byte pos (0 <= pos <= 12) of the 16-byte chunk
-__device__ __forceinline__ uint32_t dword_at(const V4 &a, int pos) { return (uint32_t)(as128(a) >> (8 * pos)); }
 
 // 16 bytes from an arbitrarily aligned source; every dword loaded holds at
 // least one of the 16 bytes, so no access leaves the source's pages.  An
@@ -373,6 +365,9 @@ __device__ __forceinline__ bool clipped_range(const Tile &T, int32_t k, int32_t 
     return a < b;
 }
 
+// One chunk, whole or clipped.  The clipped one's bytes go out as scatter's
+// few stores: byte by byte, that loop alone cost every pack kernel 20 to 40
+// registers, and the batch kernels two waves per SIMD.
 template <class AT>
 __device__ __forceinline__ void pack_chunk(const AT &at, const XferArgs &A, const Tile &T, int32_t k)
 {
@@ -381,8 +376,7 @@ __device__ __forceinline__ void pack_chunk(const AT &at, const XferArgs &A, cons
     if (!clipped_range(T, k, a, b)) return;
     const V4 acc = gather_runs(at, A.typed, (uint32_t)(T.r0 + 16 * k + a), a, b - a);
     if (b - a == 16) store_out(A, dst, u32x4{acc.w0, acc.w1, acc.w2, acc.w3});
-    else
-        for (int i = a; i < b; i++) gptr(dst)[i] = (uint8_t)byte_at(acc, i);
+    else scatter(acc, a, dst + a, b - a);
 }
 
 template <class AT>
@@ -1044,7 +1038,7 @@ __device__ __forceinline__ void runs_chunk(const XferArgs &A, const RunsCache &C
             u32x4 v = {acc.w0, acc.w1, acc.w2, acc.w3};
             store_out(A, dst, v);
         } else {
-            for (int j = (int)(a - lo); j < (int)(b - lo); j++) gptr(dst)[j] = (uint8_t)byte_at(acc, j);
+            scatter(acc, (int)(a - lo), dst + (a - lo), (int)(b - a));
         }
     }
 }

@@ -65,3 +65,11 @@ def test_unpack_kernels_keep_their_waves(kernels, policy):
     assert _waves(kernels[policy, 1, CHUNK][0]) >= 6
     assert _waves(kernels[policy, 1, ALL][0]) >= 5
     assert kernels[policy, 1, CHUNK][1] == kernels[policy, 1, ALL][1] == 0
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2])
+def test_pack_kernels_keep_their_waves(kernels, policy):
+    assert _waves(kernels[policy, 0, CHUNK][0]) >= 6
+    assert _waves(kernels[policy, 0, CHUNK | 32][0]) >= 6  # gathers through the caches
+    assert _waves(kernels[policy, 0, ALL][0]) >= 5
+    assert kernels[policy, 0, CHUNK][1] == kernels[policy, 0, ALL][1] == 0
