@@ -48,54 +48,19 @@ struct BatchHeader {
     int64_t keep_packed;    // the pack direction's output fits KEEP_PACKED_MAX: cached stores
 };
 
-// Chunks [c0, cend) of one request, with the single-request bodies.
-template <int KS>
-__device__ __forceinline__ void copy_tile_kd(const DevLayout &Ls, const DevLayout &Ld, int kd, const CopyArgs &A,
-                                             int64_t c0, int64_t cend)
+// A layout program read through the constant address space: it does not
+// change while a kernel runs, so uniform reads of it become scalar loads, as
+// they are for a layout passed by value as a kernel argument.
+__device__ __forceinline__ const DevLayout &const_layout(uint64_t addr)
 {
-    if (kd == KIND_CONTIG) copy_tile4<KS, KIND_CONTIG>(Ls, Ld, A, c0, cend);
-    else if (kd == KIND_SINGLE) copy_tile4<KS, KIND_SINGLE>(Ls, Ld, A, c0, cend);
-    else copy_tile4<KS, KIND_MULTI>(Ls, Ld, A, c0, cend);
+    return *(const DevLayout *)(const __attribute__((address_space(4))) DevLayout *)(uintptr_t)addr;
 }
 
+// Chunks [c0, cend) of a pack or an unpack, with the single-request bodies.
 template <int UNPACK, int BODY>
-__device__ __forceinline__ void run_tile(const DevLayout &L, const XferArgs &A, int body, int kind, int64_t c0,
-                                         int64_t cend, uint8_t *lds_dyn, const ReqDesc &D)
+__device__ __forceinline__ void xfer_tile(const DevLayout &L, const XferArgs &A, int body, int kind, int64_t c0,
+                                          int64_t cend, uint8_t *lds_dyn)
 {
-    if ((BODY & BODY_RELAY) && body == BODY_RELAY) {
-        // the tile's chunks are packed, then unpacked from the packed buffer
-        // by the same workgroup: after the barrier every lane sees what the
-        // others stored, still in the cache
-        constexpr int SUB = BODY & BODY_ALL;
-        XferArgs P = A;
-        P.keep = 1;
-        run_tile<0, SUB>(L, P, D.pbody, kind, c0, cend, lds_dyn, D);
-        __syncthreads();
-        const DevLayout &L2 = *(const DevLayout *)(const __attribute__((address_space(4))) DevLayout *)(uintptr_t)D.lay2;
-        XferArgs U = A;
-        U.typed = D.typed2;
-        U.elem1 = D.elem1_2;
-        run_tile<1, SUB>(L2, U, D.ubody, D.kind2, c0, cend, lds_dyn, D);
-        return;
-    }
-    if ((BODY & BODY_COPY) && body == BODY_COPY) {
-        const DevLayout &Ld = *(const DevLayout *)(const __attribute__((address_space(4))) DevLayout *)(uintptr_t)D.lay2;
-        CopyArgs C;
-        C.src = A.typed;
-        C.dst = A.packed;
-        C.off = A.off;
-        C.nbytes = A.nbytes;
-        C.nchunks = A.nchunks;
-        C.src_elem1 = A.elem1;
-        C.dst_elem1 = D.elem1_2;
-        for (int64_t s0 = c0; s0 < cend; s0 += 1024) {
-            int64_t s1 = s0 + 1024 < cend ? s0 + 1024 : cend;
-            if (kind == KIND_CONTIG) copy_tile_kd<KIND_CONTIG>(L, Ld, D.kind2, C, s0, s1);
-            else if (kind == KIND_SINGLE) copy_tile_kd<KIND_SINGLE>(L, Ld, D.kind2, C, s0, s1);
-            else copy_tile_kd<KIND_MULTI>(L, Ld, D.kind2, C, s0, s1);
-        }
-        return;
-    }
     if ((BODY & BODY_DENSE) && body == BODY_DENSE) {
         // sub-tiles sized to the type's LDS budget; LDS is reused between them
         const int64_t st = L.rec.tile_chunks;
@@ -145,6 +110,53 @@ __device__ __forceinline__ void run_tile(const DevLayout &L, const XferArgs &A, 
     }
 }
 
+// Chunks [c0, cend) of one request.  A relay's tile is packed by the code of
+// the plain packs, then unpacked from the packed buffer by the same
+// workgroup: after the barrier every lane sees what the others stored, still
+// in the cache.  A copy's two halves are chosen one after the other.  (With
+// packs of their own for relays, and a copy for every pair of kinds, the
+// kernel of every body was 1.2 MB of code instead of 0.53 with twice the
+// registers, and the batch kernels took four times as long to compile.)
+template <int UNPACK, int BODY>
+__device__ __forceinline__ void run_tile(const DevLayout &L, const XferArgs &A, int body, int kind, int64_t c0,
+                                         int64_t cend, uint8_t *lds_dyn, const ReqDesc &D)
+{
+    if ((BODY & BODY_COPY) && body == BODY_COPY) {
+        const DevLayout &Ld = const_layout(D.lay2);
+        CopyArgs C;
+        C.src = A.typed;
+        C.dst = A.packed;
+        C.off = A.off;
+        C.nbytes = A.nbytes;
+        C.nchunks = A.nchunks;
+        C.src_elem1 = A.elem1;
+        C.dst_elem1 = D.elem1_2;
+        for (int64_t s0 = c0; s0 < cend; s0 += 1024) {
+            const int64_t s1 = s0 + 1024 < cend ? s0 + 1024 : cend;
+            V4 acc[4];
+            if (kind == KIND_CONTIG) copy_gather4<KIND_CONTIG>(L, C, s0, s1, acc);
+            else if (kind == KIND_SINGLE) copy_gather4<KIND_SINGLE>(L, C, s0, s1, acc);
+            else copy_gather4<KIND_MULTI>(L, C, s0, s1, acc);
+            if (D.kind2 == KIND_CONTIG) copy_scatter4<KIND_CONTIG>(Ld, C, s0, s1, acc);
+            else if (D.kind2 == KIND_SINGLE) copy_scatter4<KIND_SINGLE>(Ld, C, s0, s1, acc);
+            else copy_scatter4<KIND_MULTI>(Ld, C, s0, s1, acc);
+        }
+        return;
+    }
+    constexpr int SUB = BODY & (BODY_ALL | BODY_CACHED);
+    const bool relay = (BODY & BODY_RELAY) && body == BODY_RELAY;
+    XferArgs P = A;
+    if (relay) P.keep = 1;
+    xfer_tile<UNPACK, SUB>(L, P, relay ? D.pbody : body, kind, c0, cend, lds_dyn);
+    if (relay) {
+        __syncthreads();
+        XferArgs U = A;
+        U.typed = D.typed2;
+        U.elem1 = D.elem1_2;
+        xfer_tile<1, SUB>(const_layout(D.lay2), U, D.ubody, D.kind2, c0, cend, lds_dyn);
+    }
+}
+
 // resets a dynamic split's tile counter before the launch (defined in batch.hip)
 __global__ void batch_counter_reset(unsigned long long *counter);
 
@@ -156,14 +168,6 @@ __device__ __forceinline__ int64_t uniform64(int64_t v)
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
     const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
     return (int64_t)(((uint64_t)hi << 32) | lo);
-}
-
-// A layout program read through the constant address space: it does not
-// change while a kernel runs, so uniform reads of it become scalar loads, as
-// they are for a layout passed by value as a kernel argument.
-__device__ __forceinline__ const DevLayout &const_layout(uint64_t addr)
-{
-    return *(const DevLayout *)(const __attribute__((address_space(4))) DevLayout *)(uintptr_t)addr;
 }
 
 // Batch kernel for one direction.  POLICY 0: tile t = blockIdx.x + k *

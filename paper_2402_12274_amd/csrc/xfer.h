@@ -556,30 +556,47 @@ __device__ __forceinline__ void scatter_stream(const DevLayout &L, uint8_t *base
 
 // A lane's chunks c0 + lane + 256u (u < 4) of a copy tile: all four are
 // gathered before any is scattered, so their loads are in flight together.
+// The two halves are separate so that a kernel of every pair of kinds holds
+// each half once per kind and not once per pair.
+template <int KS>
+__device__ __forceinline__ void copy_gather4(const DevLayout &Ls, const CopyArgs &A, int64_t c0, int64_t cend, V4 acc[4])
+{
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int64_t c = c0 + threadIdx.x + 256 * u;
+        acc[u] = V4{0u, 0u, 0u, 0u};
+        if (c < cend)
+            acc[u] = gather_stream<KS>(Ls, A.src, (uint64_t)(A.off + 16 * c), (int)min((int64_t)16, A.nbytes - 16 * c),
+                                       A.src_elem1);
+    }
+}
+
+template <int KD>
+__device__ __forceinline__ void copy_scatter4(const DevLayout &Ld, const CopyArgs &A, int64_t c0, int64_t cend,
+                                              const V4 acc[4])
+{
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+        const int64_t c = c0 + threadIdx.x + 256 * u;
+        if (c < cend)
+            scatter_stream<KD>(Ld, A.dst, (uint64_t)(A.off + 16 * c), (int)min((int64_t)16, A.nbytes - 16 * c), acc[u],
+                               A.dst_elem1);
+    }
+}
+
 template <int KS, int KD>
 __device__ __forceinline__ void copy_tile4(const DevLayout &Ls, const DevLayout &Ld, const CopyArgs &A, int64_t c0,
                                            int64_t cend)
 {
-    V4 acc0 = {0u, 0u, 0u, 0u}, acc1 = acc0, acc2 = acc0, acc3 = acc0;
-    const int64_t c = c0 + threadIdx.x;
-#define MDT_COPY_N(u) (int)min((int64_t)16, A.nbytes - 16 * (c + 256 * (u)))
-#define MDT_COPY_P(u) (uint64_t)(A.off + 16 * (c + 256 * (u)))
-    if (c < cend) acc0 = gather_stream<KS>(Ls, A.src, MDT_COPY_P(0), MDT_COPY_N(0), A.src_elem1);
-    if (c + 256 < cend) acc1 = gather_stream<KS>(Ls, A.src, MDT_COPY_P(1), MDT_COPY_N(1), A.src_elem1);
-    if (c + 512 < cend) acc2 = gather_stream<KS>(Ls, A.src, MDT_COPY_P(2), MDT_COPY_N(2), A.src_elem1);
-    if (c + 768 < cend) acc3 = gather_stream<KS>(Ls, A.src, MDT_COPY_P(3), MDT_COPY_N(3), A.src_elem1);
-    if (c < cend) scatter_stream<KD>(Ld, A.dst, MDT_COPY_P(0), MDT_COPY_N(0), acc0, A.dst_elem1);
-    if (c + 256 < cend) scatter_stream<KD>(Ld, A.dst, MDT_COPY_P(1), MDT_COPY_N(1), acc1, A.dst_elem1);
-    if (c + 512 < cend) scatter_stream<KD>(Ld, A.dst, MDT_COPY_P(2), MDT_COPY_N(2), acc2, A.dst_elem1);
-    if (c + 768 < cend) scatter_stream<KD>(Ld, A.dst, MDT_COPY_P(3), MDT_COPY_N(3), acc3, A.dst_elem1);
-#undef MDT_COPY_N
-#undef MDT_COPY_P
+    V4 acc[4];
+    copy_gather4<KS>(Ls, A, c0, cend, acc);
+    copy_scatter4<KD>(Ld, A, c0, cend, acc);
 }
 
 // The same between two regular layouts: whole chunks of one or two source
 // runs are loaded first, all of them, then scattered; the others follow one
-// at a time.  (Single launches only: the batch kernels, which carry every
-// pair of kinds, take the compiler many minutes with this body added.)
+// at a time.  (Single launches only: with it as one more body the batch
+// kernels, which already carry every kind, took the compiler half an hour.)
 __device__ __forceinline__ void copy_tile_strided(const DevStrided &Ss, const DevStrided &Sd, const CopyArgs &A,
                                                   int64_t c0, int64_t cend)
 {

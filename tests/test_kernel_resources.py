@@ -73,3 +73,14 @@ def test_pack_kernels_keep_their_waves(kernels, policy):
     assert _waves(kernels[policy, 0, CHUNK | 32][0]) >= 6  # gathers through the caches
     assert _waves(kernels[policy, 0, ALL][0]) >= 5
     assert kernels[policy, 0, CHUNK][1] == kernels[policy, 0, ALL][1] == 0
+
+
+@pytest.mark.parametrize("policy", [0, 1, 2])
+def test_kernels_hold_each_body_once(kernels, policy):
+    # relays add the unpack of every body to the packs, copies one gather and one scatter per kind: each at most about the
+    # packs' size, and a third more for register spills
+    packs = kernels[policy, 0, ALL][2]
+    assert kernels[policy, 0, COPY][2] <= packs and kernels[policy, 0, COPY][1] == 0
+    assert kernels[policy, 0, ALL | COPY][2] <= 3 * packs
+    assert kernels[policy, 0, ALL | COPY | RELAY][2] <= 4 * packs
+    assert _waves(kernels[policy, 0, ALL | COPY | RELAY][0]) >= 4
