@@ -714,7 +714,7 @@ int body_of(const DevLayout &L, const XferArgs &A, bool unpack, int32_t *lds)
         return BODY_DENSE;
     }
     if (use_short_runs(L, A)) {
-        *lds = 16 * L.short_tile + 16;
+        *lds = 16 * SHORT_STEP + 16;
         return BODY_SHORT;
     }
     if (use_runs(L)) {

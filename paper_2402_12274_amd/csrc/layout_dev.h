@@ -237,7 +237,7 @@ struct DevLayout {
     int32_t nshapes;
     int32_t dir_shift;      // directory granularity = 1 << dir_shift packed bytes
     int32_t runs_only;      // every group is a single run (varlen shape), no outer loops
-    int32_t short_tile;     // runs_only and every run short: chunks per tile of the short-run kernels, else 0
+    int32_t short_tile;     // runs_only and every run short: chunks per tile of the short-run launches, else 0
     int64_t ndir;           // directory entries
     const int64_t *gdisp;   // [G]   group displacement
     const int64_t *gpre;    // [G+1] packed-byte prefix of groups
