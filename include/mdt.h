@@ -514,9 +514,10 @@ MDT_API int mdt_batch_autotune(mdt_batch b, mdt_stream s, mdt_batch_config *best
  * a warm-up, the median decides, and all n take the winner.  mdt_batch_autotune
  * is the n = 1 case.  With the environment variable MDT_AUTOTUNE_CACHE
  * naming a file, the choice is stored there under the batch's shape (per
- * request: direction, tile body, layout kind, type size, runs per element
- * and packed bytes to a power of two; the device's compute units; the
- * library version), and a later tuning of the same shape reads it back
+ * request: direction, tile bodies, the kinds of layout program they run,
+ * type size, runs per element and packed bytes to a power of two; the
+ * device's compute units; the library version and the generation of its
+ * kernels), and a later tuning of the same shape reads it back
  * instead of timing.  The file is a JSON object, one entry per line; it is
  * rewritten through a temporary file and a rename. */
 MDT_API int mdt_batch_autotune_set(int n, mdt_batch *batches, mdt_stream s, mdt_batch_config *best);

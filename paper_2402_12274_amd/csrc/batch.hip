@@ -767,17 +767,23 @@ uint64_t fnv1a(uint64_t h, uint64_t v)
     return h;
 }
 
-// The shape of a batch: per request its direction, body, layout kind, type
-// size, runs per element and packed bytes (to a power of two), in request
-// order; plus the device's compute units and the library version.
+// Raised when a tile body or the choice of one changes: a saved tuning is a
+// choice among the kernels that it timed.
+constexpr uint64_t KERNEL_GENERATION = 2;
+
+// The shape of a batch: per request its direction, bodies, the kinds its
+// sides run as, type size, runs per element and packed bytes (to a power of
+// two), in request order; plus the device's compute units, the library
+// version and its kernels' generation.
 std::string shape_key(mdt_batch_s *b, int ncu)
 {
     uint64_t h = 1469598103934665603ull;
-    h = fnv1a(h, (uint64_t)mdt_version());
+    h = fnv1a(h, (uint64_t)mdt_version() | KERNEL_GENERATION << 32);
     h = fnv1a(h, (uint64_t)ncu);
     for (const BatchReq &r : b->reqs) {
-        h = fnv1a(h, ((uint64_t)r.d.unpack << 48) | ((uint64_t)r.d.body << 32) |
-                         (uint64_t)(uint32_t)r.type->comp->host.kind);
+        h = fnv1a(h, ((uint64_t)r.d.unpack << 48) | ((uint64_t)r.d.body << 32) | (uint64_t)(uint32_t)r.d.kind);
+        if (r.type2)
+            h = fnv1a(h, ((uint64_t)r.d.pbody << 48) | ((uint64_t)r.d.ubody << 32) | (uint64_t)(uint32_t)r.d.kind2);
         h = fnv1a(h, (uint64_t)r.type->size);
         h = fnv1a(h, (uint64_t)(r.type->comp ? r.type->comp->nruns : 0));
         h = fnv1a(h, (uint64_t)(64 - __builtin_clzll((uint64_t)r.d.nbytes | 1)));
