@@ -78,12 +78,56 @@ def _check(env, spec, count, relay_to=None):
                 assert first_diff(to_host(relay[2]), relay[1]) is None, cfg
 
 
+def _table(total, run, gap):
+    """A table of runs of `run` bytes that holds at least `total`, and the extent that it lies in."""
+    n = total // run + 1
+    return ("resized", 0, n * (run + gap) + 64, inputs.hindexed_type(np.full(n, run, np.int64), np.arange(n) * (run + gap) + 3))
+
+
 # runs of a few bytes: a step of 1024 chunks is many runs for each lane; 200 runs an element: steps of several elements
 @pytest.mark.parametrize("n,mean,longest,count", [(30000, 1, 2, 1), (12000, 12, 512, 1), (9000, 24, 256, 1), (900, 100, 512, 3),
                                                   (200, 24, 256, 40)])
 def test_short_runs(env, n, mean, longest, count):
     spec = _spec(n, mean, longest)
     total = obuild(spec).attrs()["size"] * count
-    # a relay to a table of other short runs, as long as the stream
-    lens = np.full(total // 40 + 1, 40, np.int64)
-    _check(env, spec, count, ("resized", 0, 50 * lens.size + 50, inputs.hindexed_type(lens, np.arange(lens.size) * 50 + 3)))
+    _check(env, spec, count, _table(total, 40, 10))
+
+
+# one run past the longest that a lane takes alone, a mean past theirs, runs longer than a tile's step of chunks; counts
+# of such elements
+LONG = [(5000, 24, 513, 1), (5000, 24, 513, 2), (900, 200, 4096, 1), (700, 220, 500, 3), (300, 400, 40000, 1)]
+
+
+@pytest.mark.parametrize("n,mean,longest,count", LONG)
+def test_longer_runs(env, n, mean, longest, count):
+    spec = _spec(n, mean, longest)
+    total = obuild(spec).attrs()["size"] * count
+    _check(env, spec, count, _table(total, 700, 30))
+
+
+@pytest.mark.parametrize("short_src", [False, True])
+def test_relay_between_short_and_longer_runs(env, short_src):
+    spec = _spec(4000, 24, 256 if short_src else 513)
+    total = obuild(spec).attrs()["size"]
+    _check(env, spec, 1, _table(total, 700 if short_src else 40, 20))
+
+
+@pytest.mark.parametrize("n,mean,longest,count", LONG)
+def test_longer_runs_single_launches(env, n, mean, longest, count):
+    torch, mdt = env
+    spec = _spec(n, mean, longest)
+    t, o = mdt.build_type(spec), obuild(spec)
+    host = inputs.random_bytes(count * spec[2], seed=n)
+    src = to_dev(host)
+    for i, (off, nbytes) in enumerate(RANGES):
+        ref = o.pack(host, 0, count, off, nbytes)
+        shift = 5 * i % 16
+        out, back = zeros_dev(ref.size + 32, 0xEE), zeros_dev(host.size, 0xCD)
+        assert mdt.mdt_pack(src.data_ptr(), count, t, off, out.data_ptr() + shift, nbytes) == ref.size
+        got = to_host(out)
+        assert first_diff(got[shift:shift + ref.size], ref) is None, (off, nbytes)
+        assert (got[:shift] == 0xEE).all() and (got[shift + ref.size:] == 0xEE).all(), (off, nbytes)
+        want = np.full(host.size, 0xCD, np.uint8)
+        o.unpack(ref, want, 0, count, off)
+        mdt.mdt_unpack(out.data_ptr() + shift, ref.size, back.data_ptr(), count, t, off)
+        assert first_diff(to_host(back), want) is None, (off, nbytes)
