@@ -738,8 +738,8 @@ void lower(TypeNode *t, const Layout &L, Compiled &C)
         if (D.runs_only) {
             // a lane moves its run alone, 16 bytes at a time: up to
             // SHORT_RUN_MAX bytes and SHORT_RUN_MEAN on average that is
-            // better than searching each chunk's runs; a tile holds about
-            // as many runs as a workgroup has lanes
+            // better than searching each chunk's runs (both are measured
+            // there); a tile holds about as many runs as a workgroup has lanes
             int64_t longest = 0;
             for (const Group &gr : L.groups) longest = std::max(longest, gr.len);
             if (longest <= SHORT_RUN_MAX && avg <= SHORT_RUN_MEAN)
@@ -886,7 +886,9 @@ void lower_records(const Layout &L, Compiled &C)
 // The compact program of a layout of one group: the outer loops and the
 // shape's loops as levels, and leaf runs of one length and spacing (a short
 // loop that normalisation unrolled) as one more.  Spans of one byte have no
-// 32-bit magic number and stay with the general program.
+// 32-bit magic number and stay with the general program, and so do shares of
+// a block-cyclic array that are ragged in some dimensions: several groups, or
+// leaf runs of two lengths.
 void lower_strided(const Layout &L, Compiled &C)
 {
     DevLayout &D = C.host;

@@ -188,9 +188,10 @@ __global__ __launch_bounds__(256) void xfer_kernel(const DevLayout L, const Xfer
     }
 }
 
-// regular layouts: the same tiles through the compact program, which is a
-// fifth of the general descriptor to pass (a 1.2 KB argument costs 0.75 us a
-// launch: 4.3 against 3.6 us back to back)
+// regular layouts: the same tiles through the compact program, whose 160
+// bytes are an eighth of the general descriptor to pass (empty kernels back
+// to back: 2.7 us a launch with 16 bytes of arguments, 3.3-3.5 with 128 to
+// 512, 4.0 with 1.3 KB)
 template <int NL, bool UNPACK>
 __global__ __launch_bounds__(256) void strided_kernel(const DevStrided S, const XferArgs A)
 {
@@ -207,9 +208,9 @@ __global__ __launch_bounds__(256) void strided_kernel(const DevStrided S, const 
 
 // Typed copies.  Between regular layouts the copy_strided_kernel below is
 // bound by the scattered lines of both sides: the twelve ghost-layer copies
-// of a 512^3 array took 243 us through the general program (a chunk located
+// of a 512^3 array took 240 us through the general program (a chunk located
 // by 64-bit divisions on each side, gathered word by word, a 2 MB face in 127
-// workgroups) and take 110-119 us through the compact one.
+// workgroups) and take 110 us through the compact one.
 // General form: one tile of A.tile_chunks chunks per workgroup (at most four
 // per lane)
 template <int KS, int KD>
@@ -264,8 +265,8 @@ __global__ __launch_bounds__(256) void runs_kernel(const DevLayout L, const Xfer
 }
 
 // tables of short runs: the tile's packed bytes in LDS, one run per lane (1M
-// blocks of 24 bytes: pack 82.7 -> 63.4 us, unpack 56.5 -> 51.0 us against a
-// search of each chunk's runs; the line rates put them at 36 and 50)
+// blocks of 24 bytes: pack 63.4 us, unpack 51.0; 82.7 and 56.5 by a search of
+// each chunk's runs; the line rates put them at 36 and 50)
 template <bool UNPACK>
 __global__ __launch_bounds__(256) void short_runs_kernel(const RunsTab R, const XferArgs A)
 {
@@ -384,7 +385,9 @@ static int64_t launch_grid(int64_t ntiles)
 int64_t default_tile_chunks(int64_t nchunks)
 {
     // 4 chunks per lane for large transfers, 1 for small ones (MDT_CHUNK_TILE
-    // = 64..1024 fixes it, for tuning)
+    // = 64..1024 fixes it, for tuning).  Copies of 64-byte blocks to 32-byte
+    // ones, tiles of 256 / 1024 chunks: 9.1 / 10.2 us at 4 MiB, 13.4 / 15.2
+    // at 8, 86 / 91 at 64
     static const int64_t fixed = [] {
         const char *e = getenv("MDT_CHUNK_TILE");
         int v = e && *e ? atoi(e) : 0;
@@ -420,9 +423,16 @@ bool use_dense(const DevLayout &L, const XferArgs &A, bool unpack)
     return !unpack || R.unpack_ok;
 }
 
-// A transfer that fills fewer than two workgroups per CU with the largest
-// tiles gets smaller ones, down to a wavefront's worth of chunks (64 ranges
-// of 1 MiB of records: 503 us in 64 workgroups each, 295 us in 512).
+// A transfer that fills fewer than two workgroups per CU (of 256) with the
+// largest tiles gets smaller ones, down to a wavefront's worth of chunks (64
+// ranges of 1 MiB of records: 503 us in 64 workgroups each, 280 us in 512).
+// Records of 33 bytes packed / unpacked in us, for the largest tiles only and
+// for one, two and four workgroups per CU: 7.2 / 10.7, 5.9 / 6.2, 5.5 / 5.7
+// and 6.4 / 6.4 at 1 MiB; 8.1 / 10.9, 8.2 / 10.6, 7.0 / 8.5 and 7.0 / 7.2 at
+// 4; 9.2 / 12.5, 9.1 / 12.5, 9.2 / 12.6 and 8.3 / 10.6 at 8.  A tile also
+// reads its tables, 16 KB for records of 250 or 1000 bytes, but from cache: 1
+// MiB of those takes 5.8 / 5.9 and 6.4 / 6.5, in the largest tiles 7.8 / 11.2
+// and 10.3 / 11.5.
 int64_t spread_tile(int64_t nchunks, int64_t most)
 {
     return std::min(most, std::max<int64_t>(64, (nchunks / 512 + 63) / 64 * 64));

@@ -395,7 +395,7 @@ __device__ __forceinline__ void unpack_clipped(const AT &at, const XferArgs &A, 
 // whose 16 bytes lie in one run, or in two dword-aligned runs, is loaded
 // before any store is issued, so up to four gathers per lane are in flight
 // at once.  The other chunks then take the general body, one at a time.
-// ONE_RUN: the tile lies inside the run that starts at typed.
+// A tile that lies inside one run is a copy from `one` on.
 // CACHED: the gathers load through the caches (a launch over runs shorter
 // than a line, whose lines other runs read soon after), else they stream.
 template <bool CACHED, class AT>
